@@ -65,6 +65,43 @@ QueuePlan plan_queue(uint32_t n_tiles, uint64_t tile_rows_all, uint32_t n_multi,
   return q;
 }
 
+// How the tile kernel runs a call: teams per workgroup, workgroups, and the
+// number of workers the queue is cut for (the expansion's "CUs").
+constexpr uint32_t kTwoTeamRows = 16;  // two teams for tiles of up to this many rows on average
+
+struct TilePlan {
+  uint32_t teams = 1, grid = 0, workers = 0;
+  QueuePlan q;
+};
+
+TilePlan plan_tiles(uint32_t n_tiles, uint64_t tile_rows_all, uint32_t n_multi, uint32_t one_rows_max, uint32_t cus,
+                    bool open) {
+  TilePlan t;
+  // Two teams run two short tiles per CU side by side: half the generic
+  // multiplies per tile, and one tile's end under the other's rows.  Seal calls
+  // with one team / with two, in us: 1024 segments of 1 row 67.9 / 53.5, of 4
+  // rows 110 / 98, of 16 rows 307 / 296; 300 of 16 rows 152 / 123.  In longer
+  // tiles the end does not show (64 rows: 1137 / 1134), and at the queue's end
+  // a team alone on its CU does not fill the LDS (600 segments of 20 rows: 270
+  // / 283).  With no more tiles than CUs the second team would have none;
+  // then one team, except in calls of so few rows that each CU gets one at
+  // most: 8 waves multiply sooner than 16 (11 rows: 29.4 / 27.9).
+  if (n_tiles > cus ? tile_rows_all <= (uint64_t)kTwoTeamRows * n_tiles : tile_rows_all <= cus) t.teams = 2;
+  t.workers = n_tiles > cus ? t.teams * cus : cus;
+  // A call of one-tile segments needs no finalize pass while no tile is cut.
+  // A row takes a team about 5 us, the finalize pass about 5 us of stream time
+  // and, on open, the zeroing pass behind it 4 us more, so a cut that shortens
+  // the longest tile by fewer than two rows (three on open) does not pay.
+  // With one worker no tile of up to kPieceRows rows is cut.
+  const uint64_t p = (tile_rows_all + t.workers - 1) / t.workers;
+  if (n_multi == 0 && n_tiles < t.workers && one_rows_max <= (uint32_t)kPieceRows &&
+      one_rows_max < p + (open ? 3u : 2u))
+    t.workers = 1;
+  t.q = plan_queue(n_tiles, tile_rows_all, n_multi, one_rows_max, t.workers);
+  t.grid = std::min(cus, std::max(t.q.grid, n_tiles));
+  return t;
+}
+
 // Test hook, not part of the C ABI: runs the expansion kernel on host
 // descriptors and copies its tables back (seg_cut[n], tile_base[n + 1],
 // small list[n], cap queue entries and their count).  Synchronous; it
@@ -693,7 +730,8 @@ gift_status run_gcm(const gift_tensor* t, const gift_segment_table* st, gift_key
   Plan P;
   build_plan(st->segs, n, t->n_rows, t->row_bytes, nonce_base, t->data, out, P);
   const uint32_t cus = (uint32_t)device_cus(dev);
-  const QueuePlan Q = plan_queue(P.n_tiles, P.tile_rows, P.n_multi, P.one_rows_max, cus);
+  const TilePlan TP = plan_tiles(P.n_tiles, P.tile_rows, P.n_multi, P.one_rows_max, cus, OPEN);
+  const QueuePlan& Q = TP.q;
 
   // scratch: the staged tables (descs | brief records | zero ranges | queue
   // head), then what the device builds and fills (tile_base | small list |
@@ -743,7 +781,7 @@ gift_status run_gcm(const gift_tensor* t, const gift_segment_table* st, gift_key
   // zeroes the tile partials (pieces of a cut tile XOR theirs into them) and
   // expands the segment table on the device
   const ExpandArgs ex{(uint32_t*)(scratch + o_tb), (uint32_t*)(scratch + o_sl), (TileEnt*)(scratch + o_to),
-                      (uint32_t)Q.cap, cus, nullptr, (SegInfo*)(scratch + o_si), (uint32_t*)(scratch + o_sc),
+                      (uint32_t)Q.cap, TP.workers, nullptr, (SegInfo*)(scratch + o_si), (uint32_t*)(scratch + o_sc),
                       kSmallMaxBlocks};
   const SegDesc* d_desc = (const SegDesc*)(scratch + o_desc);
   gift_status rs = GIFT_OK;
@@ -783,7 +821,7 @@ gift_status run_gcm(const gift_tensor* t, const gift_segment_table* st, gift_key
           return e;
         }
       }
-      e = launch_gcm_tiles(a, OPEN ? kModeOpen : 0, Q.grid, stream);
+      e = launch_gcm_tiles(a, OPEN ? kModeOpen : 0, TP.grid, TP.teams, stream);
       if (e != hipSuccess) {
         rs = hip_fail(e, "gcm launch");
         return e;
@@ -966,7 +1004,8 @@ gift_status run_paged(const gift_paged_kv* kv, const gift_request* reqs, uint32_
   uint32_t shift = 0;
   while ((16ull << shift) < kv->chunk_bytes) shift++;
   const uint32_t cus = (uint32_t)device_cus(dev);
-  const QueuePlan Q = plan_queue(n_tiles, tile_rows_all, n_multi, one_rows_max, cus);
+  const TilePlan TP = plan_tiles(n_tiles, tile_rows_all, n_multi, one_rows_max, cus, OPEN);
+  const QueuePlan& Q = TP.q;
 
   // scratch: the staged tables (descs | brief records | block ids | queue
   // head), then what the device builds and fills (tile_base | small list |
@@ -1008,7 +1047,7 @@ gift_status run_paged(const gift_paged_kv* kv, const gift_request* reqs, uint32_
   // the prologue copies the tables, settles the verdicts (owner check by
   // block id), zeroes the tile partials and expands the segment table
   const ExpandArgs ex{(uint32_t*)(scratch + o_tb), (uint32_t*)(scratch + o_sl), (TileEnt*)(scratch + o_to),
-                      (uint32_t)Q.cap, cus, nullptr, (SegInfo*)(scratch + o_si), (uint32_t*)(scratch + o_sc), 0u};
+                      (uint32_t)Q.cap, TP.workers, nullptr, (SegInfo*)(scratch + o_si), (uint32_t*)(scratch + o_sc), 0u};
   gift_status rs = GIFT_OK;
   EventMark call_ev;  // the event recorded behind the call's last kernel
   const SegDesc* d_desc = (const SegDesc*)(scratch + o_desc);
@@ -1053,7 +1092,7 @@ gift_status run_paged(const gift_paged_kv* kv, const gift_request* reqs, uint32_
         return e;
       }
     }
-    e = launch_gcm_tiles(a, OPEN ? (kModeOpen | kModeScatter) : kModeGather, Q.grid, stream);
+    e = launch_gcm_tiles(a, OPEN ? (kModeOpen | kModeScatter) : kModeGather, TP.grid, TP.teams, stream);
     if (e == hipSuccess && g_prof_after) e = hipEventRecord(g_prof_after, stream);
     if (e == hipSuccess) e = launch_gcm_finalize(a, OPEN, stream);
     if (e == hipSuccess && OPEN)
@@ -1143,8 +1182,7 @@ gift_status gift_key_table_create(const uint8_t* keys, uint32_t n_users, hipStre
   const size_t o_dk = o_rk + align256(u * 64 * 4);
   const size_t o_h = o_dk + align256(u * 64 * 4);
   const size_t o_gt = o_h + align256(u * 16);
-  const size_t o_gf = o_gt + align256(u * 512 * 16);
-  const size_t o_ph = o_gf + align256(u * 512 * 16);
+  const size_t o_ph = o_gt + align256(u * 2 * 512 * 16);
   const size_t o_pt = o_ph + align256(u * kHPowers * 16);
   const size_t o_pl = o_pt + align256(u * kFinLanes * 16);
   const size_t o_px = o_pl + align256(u * 16);
@@ -1168,7 +1206,6 @@ gift_status gift_key_table_create(const uint8_t* keys, uint32_t n_users, hipStre
   kt->dev.dk = (uint32_t*)(mem + o_dk);
   kt->dev.h = (uint32_t*)(mem + o_h);
   kt->dev.gtab = (uint4*)(mem + o_gt);
-  kt->dev.gtab_fold = (uint4*)(mem + o_gf);
   kt->dev.pow_h = (uint4*)(mem + o_ph);
   kt->dev.pow_ht = (uint4*)(mem + o_pt);
   kt->dev.pow_hlt = (uint4*)(mem + o_pl);

@@ -23,13 +23,9 @@ constexpr int kRows = GIFT_ROWS;
 constexpr uint32_t kTileBlocks = (uint32_t)kThreads * kRows;  // 2 MiB per tile by default
 static_assert(kThreads % 64 == 0 && kThreads <= 1024, "workgroup size");
 constexpr uint32_t kSmallMaxBlocks = 64;                   // segments up to 1 KiB: one wave each
-constexpr int kHPowers = kThreads + 2;                     // H^0 .. H^(kThreads+1) per user
 constexpr int kHxLanes = 64;                               // H * x^(64+k), k < 64, per user
 constexpr int kFinLanes = 64;                              // lanes of the per-segment finalize
-// Tile end of the per-block kernel: one leader wave per SIMD folds the lane
-// partials of kThreads / 64 / kLeaders waves with W = H^(64 * kLeaders).
-constexpr int kLeaders = 4;
-static_assert(kThreads % (64 * kLeaders) == 0, "waves per leader");
+constexpr int kHPowers = kThreads + 2;                     // H^0 .. H^(kThreads+1) per user
 
 // kSegOneTile: a tiled segment of at most kTileBlocks blocks; unless its tile
 // is cut into pieces, the tile kernel writes its tag (open: its verdict)
@@ -66,8 +62,7 @@ struct KeyTableDev {
   uint32_t* rk;      // [n_users][64] round-key words (60 used)
   uint32_t* dk;      // [n_users][64] equivalent-inverse-cipher round keys (60 used)
   uint32_t* h;       // [n_users][4]  H = E_K(0^128)
-  uint4* gtab;       // [n_users][32][16] 4-bit GHASH tables of M = H^kThreads
-  uint4* gtab_fold;  // [n_users][32][16] 4-bit GHASH tables of W = H^(64 * kLeaders)
+  uint4* gtab;       // [n_users][2][32][16] 4-bit GHASH tables of M = H^kThreads and H^(kThreads / 2)
   uint4* pow_h;      // [n_users][kHPowers] H^k
   uint4* pow_ht;     // [n_users][kFinLanes] H^(k * kTileBlocks)
   uint4* pow_hlt;    // [n_users] H^(kFinLanes * kTileBlocks)
@@ -195,7 +190,8 @@ hipError_t launch_expand(const SegBrief* brief, uint32_t n_segs, const ExpandArg
 inline uint64_t queue_capacity(uint32_t n_tiles, uint32_t cus) {
   return (uint64_t)n_tiles + (uint64_t)(kRows / kPieceRows - 1) * cus;
 }
-hipError_t launch_gcm_tiles(const GcmArgs& a, int mode, uint32_t grid, hipStream_t s);
+// grid workgroups of one or two teams (see plan_tiles)
+hipError_t launch_gcm_tiles(const GcmArgs& a, int mode, uint32_t grid, uint32_t teams, hipStream_t s);
 hipError_t launch_gcm_small(const GcmArgs& a, bool open, hipStream_t s);
 hipError_t launch_gcm_finalize(const GcmArgs& a, bool open, hipStream_t s);
 hipError_t launch_zero_ranges(uint8_t* out, const ZeroRange* r, uint32_t n, const int32_t* verdicts, uint32_t grid,

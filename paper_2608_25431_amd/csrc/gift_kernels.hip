@@ -1,24 +1,25 @@
 // gfx950 kernels for segmented, per-user AES-256-GCM and the owner check.
 //
-// Hot path (k_gcm_tiles): one workgroup of 1024 threads per CU, persistent
-// over 2 MiB tiles.  Each lane handles one 16-byte block per 1024-block row:
+// Hot path (k_gcm_tiles): one workgroup of 1024 threads per CU, its waves one
+// team or two, each team persistent over 2 MiB tiles.  Each lane handles one
+// 16-byte block per row of its team (1024 or 512 blocks):
 //   - AES-256-CTR keystream from four T-tables in LDS, each replicated 32x so
 //     that lane l reads copy (l mod 32) and a wave's random lookups never
 //     collide in a bank; one v_perm_b32 forms each lookup address;
 //   - one coalesced 16-byte load, XOR, 16-byte store;
-//   - GHASH by per-lane Horner with M = H^1024: Y <- Y*M xor X, where the
+//   - GHASH by per-lane Horner with M = H^row: Y <- Y*M xor X, where the
 //     multiply by the fixed M uses 32 nibble-indexed tables (8 KiB per user)
 //     staged in LDS.
 // Tiles are aligned to the END of their segment, so the block at distance d
 // from the segment's last block contributes X*H^(d + 2) to the GHASH sum; a
 // tile t contributes P_t * H^(t*T) with P_t = sum of X*H^(d_t + 2) over its
 // own blocks (d_t: distance from the tile's end), and lane l of a full tile
-// ends at distance (1023 - l) from the tile's end.  At tile end one leader
-// wave per SIMD folds the lane partials of four waves with LDS tables of
-// H^256 and applies the remaining per-lane power with one generic multiply,
-// while the other waves prefetch the next tile.  The host cuts some tiles
-// into row pieces (every tile when a call has fewer tiles than CUs, else up
-// to one per CU at the queue's tail), whose partials meet by XOR.
+// ends at distance (row - 1 - l) from the tile's end.  Each wave multiplies
+// its lanes' sums by their powers (one generic multiply) and XORs the wave's
+// sum into the tile's; the last wave of the team to do so finishes the tile,
+// while the others are in the next one.  The expansion cuts some tiles into
+// row pieces (every tile when a call has fewer tiles than teams, else up to
+// one per team at the queue's tail), whose partials meet by XOR.
 //
 // Around it: k_prologue (first kernel of a call: staged tables from pinned
 // host memory, owner check, E_K(J0) xor H*L of one-tile segments),
@@ -39,27 +40,76 @@ __constant__ AesConst c_aes = make_aes_const();
 
 constexpr int32_t kVerdictOk = 0, kVerdictAuthFail = 1, kVerdictOwnerMixed = 2;
 
-// LDS layout of k_gcm_tiles (bytes).
-constexpr uint32_t kLdsGtab = 0;                    // 32 x 16 x 16 B GHASH tables of M
-constexpr uint32_t kLdsAes = 8192;                  // T0/T1 (64 KiB) then T2/T3 (64 KiB)
-constexpr uint32_t kLdsFold = kLdsAes + 131072;     // 32 x 16 x 16 B GHASH tables of W
-constexpr uint32_t kLdsStage = kLdsFold + 8192;     // lane partials of the waves that are not leaders
-// one 16 B slot per leader, then E_K(J0) xor H*L of a one-tile segment
-constexpr uint32_t kLdsRed = kLdsStage + 16 * (kThreads - 64 * kLeaders);
-constexpr uint32_t kLdsInfo = kLdsRed + 16 * (kLeaders + 1);  // TileInfo of the current tile
+// LDS of k_gcm_tiles: the GHASH tables of each team, the AES tables (T0/T1,
+// then T2/T3, 64 KiB each), the state of each team.
+constexpr uint32_t kGtabBytes = 8192;  // 32 x 16 x 16 B GHASH tables of M
 
-// The current tile's record in LDS, staged by the prefetch waves.
+// A tile's record in LDS.
 struct TileInfo {
   uint32_t g, s, trow, user;  // queue entry
   int32_t verdict;
-  uint32_t next_k;  // queue entry claimed for the next tile
-  uint32_t pad[2];
+  uint32_t pad[3];
   uint4 fin;  // one-tile segment: E_K(J0) xor H*L from the prologue
   SegDesc desc;
   uint32_t rk[64];  // round keys (60 used)
 };
-constexpr uint32_t kLdsBytes = kLdsInfo + sizeof(TileInfo);
-static_assert(kLdsBytes <= 160u * 1024u, "LDS of a gfx950 workgroup");
+// The sum of a tile and how far its team is with it.
+struct TileSum {
+  uint32_t z[4];   // XOR of the waves' sums
+  uint32_t rows;   // waves that have done their rows
+  uint32_t done;   // waves whose sum is in z
+  uint32_t pad[2];
+};
+constexpr uint32_t kSlots = 4;  // tiles of a team that can be under way at once
+// How the waves of a team follow each other through its tiles k = 0, 1, ...
+// (see k_gcm_tiles).
+struct TeamState {
+  TileInfo info[kSlots];
+  TileSum sum[kSlots];
+  uint32_t rec;    // k + 1 once the records of tiles 0..k are in LDS
+  uint32_t mtab;   // k + 1 once the tables of M hold tile k's user
+  uint32_t fin;    // k + 1 once tiles 0..k are finished
+  uint32_t pad;
+};
+// Offsets, and what a team is, with TEAMS teams per workgroup.
+template <int TEAMS>
+struct Team {
+  static constexpr uint32_t threads = kThreads / TEAMS, waves = threads / 64;
+  static constexpr int rows = kRows * TEAMS;  // rows of `threads` blocks per tile
+  static constexpr uint32_t lds_aes = TEAMS * kGtabBytes, lds_state = lds_aes + 131072;
+  static constexpr uint32_t lds_bytes = lds_state + TEAMS * sizeof(TeamState);
+  static_assert(lds_bytes <= 160u * 1024u, "LDS of a gfx950 workgroup");
+};
+
+// a value that is the same in every lane, in scalar registers
+__device__ __forceinline__ uint64_t uniform64(uint64_t v) {
+  // (the builtin's result is a signed int)
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)v);
+  return ((uint64_t)hi << 32) | lo;
+}
+
+// Counters in LDS between the waves of one workgroup, which are all resident
+// until they end, so a wait for work that another wave does without waiting
+// for this one ends.  wave_arrive and wave_set publish the wave's LDS writes
+// before the count; wave_wait orders its later LDS accesses after it.
+__device__ __forceinline__ uint32_t wave_arrive(uint32_t* c) {  // returns the arrivals before this one
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  uint32_t n = 0;
+  if ((threadIdx.x & 63u) == 0u) n = __hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  return (uint32_t)__builtin_amdgcn_readfirstlane(n);
+}
+__device__ __forceinline__ void wave_set(uint32_t* c, uint32_t v) {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  if ((threadIdx.x & 63u) == 0u) __hip_atomic_store(c, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void wave_wait(const uint32_t* c, uint32_t v) {
+  while ((int32_t)(__builtin_amdgcn_readfirstlane(
+                       __hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) - v) < 0)
+    __builtin_amdgcn_s_sleep(1);
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
 
 __device__ __forceinline__ uint32_t lds32(const uint8_t* base, uint32_t off) {
   return *(const uint32_t*)(base + off);
@@ -150,12 +200,13 @@ __device__ __forceinline__ void ctr_rounds12(CtrCache& c, uint32_t ctr, uint32_t
   const uint32_t s3 = bswap32(ctr) ^ rk[3];
   if ((ctr >> 16) != c.hi) {  // rare and per lane
     c.hi = ctr >> 16;
+    const uint32_t in0 = opaque(c.in0);  // its lookups stay here, not held in registers across the rows
     c.in2 = c.u2 ^ GIFT_T1(s3, 1);
     c.in3 = c.u3 ^ GIFT_T0(s3, 0);
-    c.w0 = xor3(GIFT_T0(c.in0, 0), GIFT_T2(c.in2, 2), GIFT_T3(c.in3, 3)) ^ rk[8];
-    c.w1 = xor3(GIFT_T1(c.in2, 1), GIFT_T2(c.in3, 2), GIFT_T3(c.in0, 3)) ^ rk[9];
-    c.w2 = xor3(GIFT_T0(c.in2, 0), GIFT_T1(c.in3, 1), GIFT_T2(c.in0, 2)) ^ rk[10];
-    c.w3 = xor3(GIFT_T0(c.in3, 0), GIFT_T1(c.in0, 1), GIFT_T3(c.in2, 3)) ^ rk[11];
+    c.w0 = xor3(GIFT_T0(in0, 0), GIFT_T2(c.in2, 2), GIFT_T3(c.in3, 3)) ^ rk[8];
+    c.w1 = xor3(GIFT_T1(c.in2, 1), GIFT_T2(c.in3, 2), GIFT_T3(in0, 3)) ^ rk[9];
+    c.w2 = xor3(GIFT_T0(c.in2, 0), GIFT_T1(c.in3, 1), GIFT_T2(in0, 2)) ^ rk[10];
+    c.w3 = xor3(GIFT_T0(c.in3, 0), GIFT_T1(in0, 1), GIFT_T3(c.in2, 3)) ^ rk[11];
   }
   const uint32_t in1 = c.u1 ^ GIFT_T2(s3, 2);
   x0 = c.w0 ^ GIFT_T1(in1, 1);
@@ -213,37 +264,6 @@ __device__ __forceinline__ u128 ghash_step_lds(const u128& y, const u128& x, con
       a2 = xor3(a2, e[k].z, e[k + 1].z);
       a3 = xor3(a3, e[k].w, e[k + 1].w);
     }
-  }
-  return u128{{a0, a1, a2, a3}};
-}
-
-// The same product for the tile end, one word of y (eight table reads) per
-// loop iteration: the words rotate through w0, so nothing is indexed at run
-// time, and the fold stays within the registers a call may clobber (more in
-// flight would make it save callee-saved registers to scratch at every tile
-// end).
-__device__ __forceinline__ u128 ghash_step_lds_lean(const u128& y, const u128& x, const uint8_t* gt) {
-  uint32_t a0 = x.w[0], a1 = x.w[1], a2 = x.w[2], a3 = x.w[3];
-  uint32_t w0 = y.w[0], w1 = y.w[1], w2 = y.w[2], w3 = y.w[3];
-#pragma unroll 1
-  for (int j = 0; j < 4; j++) {
-    const uint8_t* g = gt + j * 8 * 256;
-    uint4 e[8];
-#pragma unroll
-    for (int k = 0; k < 4; k++) {
-      e[2 * k] = lds128(g + (2 * k) * 256, nib_hi16(w0, k));
-      e[2 * k + 1] = lds128(g + (2 * k + 1) * 256, nib_lo16(w0, k));
-    }
-#pragma unroll
-    for (int k = 0; k < 8; k += 2) {
-      a0 = xor3(a0, e[k].x, e[k + 1].x);
-      a1 = xor3(a1, e[k].y, e[k + 1].y);
-      a2 = xor3(a2, e[k].z, e[k + 1].z);
-      a3 = xor3(a3, e[k].w, e[k + 1].w);
-    }
-    w0 = w1;
-    w1 = w2;
-    w2 = w3;
   }
   return u128{{a0, a1, a2, a3}};
 }
@@ -308,39 +328,87 @@ __device__ __forceinline__ u128 length_block(uint64_t len) {
   return u128{{0u, 0u, bswap32((uint32_t)(bits >> 32)), bswap32((uint32_t)bits)}};
 }
 
-// Tile end of a leader wave (see k_gcm_tiles): Horner over the staged lane
-// partials of its waves in W (LDS tables), one multiply by the lane's power
-// hp, then the wave sum into the leader's reduction slot.  Kept out of line,
-// so that the main loop's register allocation does not see it (inlined, the
-// kernel spills twice as many registers); the LDS regions arrive as byte
-// offsets in the LDS address space, so every access is an LDS instruction.
-typedef __attribute__((address_space(3))) uint8_t lds_byte;
-__device__ __noinline__ void tile_fold(u128 v, uint32_t stage_off, uint32_t wt_off, u128 hp, uint32_t red_off,
-                                       uint32_t lane) {
-  constexpr int kFold = kThreads / 64 / kLeaders;
-  const u128* stage = (const u128*)(lds_byte*)(uintptr_t)stage_off;
-  const uint8_t* wt = (const uint8_t*)(lds_byte*)(uintptr_t)wt_off;
-#pragma unroll 1
-  for (int i = 1; i < kFold; i++) v = ghash_step_lds_lean(v, stage[64u * kLeaders * (i - 1)], wt);
-  u128 z = gf_mul(v, hp);
+// A wave's share of a tile's sum: each lane's y times the lane's power hp,
+// summed over the wave (the result is wave-uniform).  Kept out of line, so
+// that the main loop's register allocation does not see the multiply
+// (inlined, the kernel spills).
+__device__ __noinline__ u128 wave_sum_of(u128 y, u128 hp) {
+  u128 z = gf_mul(y, hp);
 #pragma unroll
   for (int j = 0; j < 4; j++) z.w[j] = wave_xor(z.w[j]);
-  if (lane == 0) *(u128*)(lds_byte*)(uintptr_t)red_off = z;
+  return z;
 }
 
 // ---------------------------------------------------------------------------
 // Per-block kernel over 2 MiB tiles of the non-small segments.
 // ---------------------------------------------------------------------------
-template <int MODE>
+template <int MODE, int TEAMS>
 __global__ __launch_bounds__(kThreads) void k_gcm_tiles(GcmArgs a) {
+  constexpr uint32_t kTeamThreads = Team<TEAMS>::threads, kTeamWaves = Team<TEAMS>::waves;
+  constexpr int kTeamRows = Team<TEAMS>::rows;
   constexpr bool OPEN = (MODE & kModeOpen) != 0;
   constexpr bool GATHER = (MODE & kModeGather) != 0, SCATTER = (MODE & kModeScatter) != 0;
-  __shared__ __attribute__((aligned(16))) uint8_t smem[kLdsBytes];
-  __shared__ uint32_t tile_failed;  // open: the tag of the tile's one-tile segment did not match
+  __shared__ __attribute__((aligned(16))) uint8_t smem[Team<TEAMS>::lds_bytes];
   const uint32_t tid = threadIdx.x;
-  uint8_t* tt = smem + kLdsAes;
-  const uint8_t* gt = smem + kLdsGtab;
-  u128* red = (u128*)(smem + kLdsRed);
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t team = wave / kTeamWaves, tw = wave % kTeamWaves;
+  uint8_t* tt = smem + Team<TEAMS>::lds_aes;
+  TeamState* const ts = (TeamState*)(smem + Team<TEAMS>::lds_state) + team;
+
+  // The record of queue entry i, by one wave (lane l of it).
+  auto load_record = [&](TileInfo* t, uint32_t i, uint32_t l) {
+    const TileEnt e = i < a.n_ents ? a.tile_order[i] : TileEnt{kNoTile, 0u, 0u, 0u};
+    if (l == 0u) *(uint4*)t = make_uint4(e.g, e.s, e.trow, e.user);
+    if (e.g == kNoTile) return;
+    t->rk[l] = a.kt.rk[(size_t)e.user * 64u + l];
+    if (l < 16u) ((uint32_t*)&t->desc)[l] = ((const uint32_t*)(a.segs + e.s))[l];
+    if (l == 16u) t->verdict = a.verdicts[e.s];
+    if (l == 17u) t->fin = a.fin[e.s];  // meaningful for one-tile segments only
+  };
+  // the tables of M of a user, by one wave: two calls, so that the loads can
+  // be in flight while the team finishes with the tables before them
+  struct Tables {
+    u32x4 e0, e1, e2, e3, e4, e5, e6, e7;
+  };
+  auto read_tables = [&](uint32_t user, uint32_t l) -> Tables {
+    const u32x4* src = (const u32x4*)(a.kt.gtab + ((size_t)user * 2u + (TEAMS - 1u)) * 512u) + l;
+    return Tables{src[0], src[64], src[128], src[192], src[256], src[320], src[384], src[448]};
+  };
+  auto write_tables = [&](const Tables& m, uint32_t l) {
+    u32x4* dst = (u32x4*)(smem + team * kGtabBytes) + l;
+    dst[0] = m.e0, dst[64] = m.e1, dst[128] = m.e2, dst[192] = m.e3;
+    dst[256] = m.e4, dst[320] = m.e5, dst[384] = m.e6, dst[448] = m.e7;
+  };
+
+  // Work queue over the expansion's order (longest entries first): team w of
+  // W takes entry w first, then entries W + (queue claims).  Two teams per
+  // workgroup run short tiles, most often two each: there the second entry is
+  // 2W - 1 - w (the longest with the shortest), known at the start.
+  //
+  // The waves of a team go through its tiles without a barrier, each at its
+  // own pace, so that one tile's end (the generic multiplies, VALU work of
+  // about 900 instructions per wave) overlaps LDS work of the other waves:
+  //   - kRecWave, of the oldest waves, which the SIMDs favour and which finish
+  //     first, fetches tile k + 1's record (queue claim, entry, descriptor and
+  //     round keys: three dependent loads, up to 12k clocks).  In a tile of
+  //     more than kLateRows rows it does so after its rows, so that a
+  //     workgroup claims no more than it is about to run; else before them.
+  //     The slot held tile k - 3, which is finished.
+  //   - a wave that has done its rows of tile k multiplies, adds to the tile's
+  //     sum and goes on to tile k + 1, whose first row needs no GHASH table.
+  //   - kTabWave, of the youngest, writes the tables of tile k + 1's user once
+  //     every wave of the team has done its rows of tile k.
+  //   - the last wave to add its sum finishes the tile.
+  // Against barriers around the tile's end and four leader waves folding all
+  // partials there (per-phase clocks: LDS idle for 46% of the time with 1-4
+  // rows per tile): 1024 segments of 16-64 KiB 80.4 -> 74.0 us per call with
+  // two teams (81 with one); 2 requests, 45 tiles cut into 25-row pieces, 159.9
+  // -> 144.2 us; 128-row tiles +0.7%.
+  constexpr uint32_t kRecWave = 0, kTabWave = kTeamWaves - 1;
+  constexpr int kLateRows = 16 * TEAMS;
+  constexpr bool kPair = TEAMS == 2;  // the second entry is 2W - 1 - w
+  const uint32_t W = TEAMS * gridDim.x, w = blockIdx.x + team * gridDim.x;
+  const TileEnt e0 = w < a.n_ents ? a.tile_order[w] : TileEnt{kNoTile, 0u, 0u, 0u};
 
   // Replicated T-tables: word w = region*16384 + x*64 + slot holds
   // T_{2*region + slot/32}[x] = rotl(Te0[x], 8*table).  Four consecutive
@@ -355,90 +423,55 @@ __global__ __launch_bounds__(kThreads) void k_gcm_tiles(GcmArgs a) {
     ((uint4*)tt)[q] = make_uint4(r, r, r, r);
   }
   const uint32_t L = ((tid & 31u) << 2) | 0x10000u;  // this lane's table copy
-  uint32_t cur_user = 0xFFFFFFFFu;  // user whose GHASH tables are in LDS
-  TileInfo* ti = (TileInfo*)(smem + kLdsInfo);
+  // the first tile's tables, the first two records
+  if (tw == kTabWave && e0.g != kNoTile) write_tables(read_tables(e0.user, tid & 63u), tid & 63u);
+  if (tw == kRecWave) load_record(&ts->info[0], w, tid & 63u);
+  if (kPair && tw == 1) load_record(&ts->info[1], 2u * W - 1u - w, tid & 63u);
+  if (tw == 2) {
+    if ((tid & 63u) < kSlots) ts->sum[tid & 63u] = TileSum{{0u, 0u, 0u, 0u}, 0u, 0u, {0u, 0u}};
+    if ((tid & 63u) == 0u) ts->rec = kPair ? 2u : 1u, ts->mtab = 1u, ts->fin = 0u;
+  }
+  __syncthreads();
 
-  // Work queue over the host's tile order (longest tiles first): workgroup b
-  // takes entry b first, then entries gridDim.x + (queue claims); the claim
-  // is issued when a tile starts.  While the leader waves fold a tile's GHASH
-  // partials, the other waves (the prefetch waves) load the next tile's
-  // entry, descriptor, verdict, round keys and, for a new user, the tables of
-  // M into LDS (nothing reads them then) and the tables of W into registers
-  // (the fold still reads W), so no global-memory latency sits between two
-  // tiles.  Every wave leaves the loop on the same entry.
-  constexpr uint32_t kPf0 = 64u * kLeaders;  // first thread of the prefetch waves
-  static_assert(kThreads - kPf0 > 593u, "prefetch roles");
-  uint32_t claim = 0;  // thread kPf0: queue entry of the next tile
-  bool pf_tabs = false;  // this thread holds entry j of the next user's W tables
-  uint4 pf_w = make_uint4(0u, 0u, 0u, 0u);
-  // thread kPf0 + j: j < 512 tables; 512 + i descriptor word i (i < 16);
-  // 528 + i round-key word i (i < 64); 592 entry and verdict; 593 fin
-  auto prefetch = [&](uint32_t k) {
-    const uint32_t j = opaque(tid) - kPf0;
-    const TileEnt e = k < a.n_ents ? a.tile_order[k] : TileEnt{kNoTile, 0u, 0u, 0u};
-    if (j == 592u) {
-      ti->g = e.g;
-      ti->s = e.s;
-      ti->trow = e.trow;
-      ti->user = e.user;
-    }
-    if (e.g == kNoTile) return;
-    const uint32_t u = e.user;
-    if (j < 512u) {
-      if (u != cur_user) {
-        pf_tabs = true;
-        ((uint4*)(smem + kLdsGtab))[j] = a.kt.gtab[(size_t)u * 512u + j];
-        pf_w = a.kt.gtab_fold[(size_t)u * 512u + j];
-      }
-    } else if (j < 528u) {
-      ((uint32_t*)&ti->desc)[j - 512u] = ((const uint32_t*)(a.segs + e.s))[j - 512u];
-    } else if (j < 592u) {
-      ti->rk[j - 528u] = a.kt.rk[(size_t)u * 64u + (j - 528u)];
-    } else if (j == 592u) {
-      ti->verdict = a.verdicts[e.s];
-    } else if (j == 593u) {
-      ti->fin = a.fin[e.s];  // meaningful for one-tile segments only
-    }
+  auto fetch_next = [&](uint32_t k, uint32_t l) {
+    if (kPair && k == 0u) return;
+    uint32_t c = 0;
+    if (l == 0u) c = atomicAdd(a.tile_counter, 1u);
+    c = (uint32_t)__builtin_amdgcn_readfirstlane(c) + (kPair ? 2u * W : W);
+    wave_wait(&ts->fin, k - 2u);
+    load_record(&ts->info[(k + 1u) % kSlots], c, l);
+    wave_set(&ts->rec, k + 2u);
   };
-  auto commit = [&]() {
-    if (pf_tabs) ((uint4*)(smem + kLdsFold))[tid - kPf0] = pf_w;
-    // dead until the next prefetch (which the leader waves never run): not
-    // carried across the tile
-    pf_tabs = false;
-    pf_w = make_uint4(0u, 0u, 0u, 0u);
-  };
-  if (tid >= kPf0) prefetch(blockIdx.x);
-
-  for (;;) {
-    commit();
-    __syncthreads();  // the tile's record and tables are in LDS; the previous tile is done with them
+  for (uint32_t k = 0;; k++) {
+    wave_wait(&ts->rec, k + 1u);
+    const TileInfo* ti = &ts->info[k % kSlots];
     const uint32_t g = __builtin_amdgcn_readfirstlane(ti->g);
     if (g == kNoTile) break;
     // the thread index, recomputed per tile: per-lane values derived from it
     // are formed here, not hoisted to the kernel's start and held (or
     // spilled) across every tile
-    const uint32_t tid_t = opaque(tid);
-    if (tid_t == kPf0) claim = gridDim.x + atomicAdd(a.tile_counter, 1u);
+    const uint32_t tid_t = opaque(tid) % kTeamThreads;
     const uint32_t s = __builtin_amdgcn_readfirstlane(ti->s);
     const uint32_t trow = __builtin_amdgcn_readfirstlane(ti->trow);
     const uint32_t t = trow & 0xFFFFu;                                      // tile of the segment
-    const int r0 = (int)((trow >> 16) & 0xFFu), r1 = (int)(trow >> 24);  // its rows in this entry
+    // its rows in this entry, in the team's rows
+    const int r0 = TEAMS * (int)((trow >> 16) & 0xFFu), r1 = TEAMS * (int)(trow >> 24);
     const uint32_t user = __builtin_amdgcn_readfirstlane(ti->user);
     const int32_t verdict = (int32_t)__builtin_amdgcn_readfirstlane((uint32_t)ti->verdict);
-    cur_user = user;
     const uint32_t m = __builtin_amdgcn_readfirstlane(ti->desc.nblocks);
-    const uint64_t off = ti->desc.byte_off, len = ti->desc.len;
+    const uint64_t off = uniform64(ti->desc.byte_off), len = uniform64(ti->desc.len);
     const uint32_t flags = __builtin_amdgcn_readfirstlane(ti->desc.flags);
     const bool aligned = (flags & kSegAligned) != 0;
     // a one-tile segment whose tile is cut into pieces gets its tag from the finalize pass
-    const bool one = (flags & kSegOneTile) != 0 && r0 == 0 && r1 == kRows;
-    if (one && tid_t == 0) red[kLeaders] = u128{{ti->fin.x, ti->fin.y, ti->fin.z, ti->fin.w}};  // for the tile end
+    const bool one = (flags & kSegOneTile) != 0 && r0 == 0 && r1 == kTeamRows;
     const int64_t base = (int64_t)m - (int64_t)(t + 1) * (int64_t)kTileBlocks;  // block index of virtual slot 0
-    const int r_start = base < 0 ? (int)((uint64_t)(-base) / kThreads) : 0;
+    const int r_start = base < 0 ? (int)((uint64_t)(-base) / kTeamThreads) : 0;
     const int r_lo = r_start > r0 ? r_start : r0;
+    const bool late = r1 - r_lo > kLateRows;
+    if (tw == kRecWave && !late) fetch_next(k, tid_t & 63u);
 
     // paged side: block i of the segment lives in chunk i >> shift
-    const uint64_t chunk0 = ti->desc.chunk0;
+    const uint64_t chunk0 = uniform64(ti->desc.chunk0);
     const uint64_t cmask = (1ull << a.chunk_shift) - 1;
     auto paged = [&](uint64_t i) -> uint8_t* {
       return a.pbase + a.chunk_off[chunk0 + (i >> a.chunk_shift)] + ((i & cmask) << 4);
@@ -460,11 +493,12 @@ __global__ __launch_bounds__(kThreads) void k_gcm_tiles(GcmArgs a) {
       // scatter into the cache writes nothing at all: the request's table
       // names a block of another owner, which keeps its contents.
       if (!SCATTER) {
+        const uint32_t z = opaque(0u);  // formed here, not held from the kernel's start
         for (int r = r_lo; r < r1; r++) {
-          const int64_t i0 = base + (int64_t)r * kThreads + tid_t;
+          const int64_t i0 = base + (int64_t)r * kTeamThreads + tid_t;
           if (i0 >= 0) {
             const uint64_t rem = len - 16ull * (uint64_t)i0;
-            store_block(a.out + off + 16ull * (uint64_t)i0, u128_zero(), rem >= 16 ? 16u : (uint32_t)rem, aligned);
+            store_block(a.out + off + 16ull * (uint64_t)i0, u128{{z, z, z, z}}, rem >= 16 ? 16u : (uint32_t)rem, aligned);
           }
         }
       }
@@ -475,8 +509,8 @@ __global__ __launch_bounds__(kThreads) void k_gcm_tiles(GcmArgs a) {
 
       // rows where every lane holds a whole block and the segment is 16-byte
       // aligned take the branch-free path
-      const int r_full = base < 0 ? (int)(((uint64_t)(-base) + kThreads - 1) / kThreads) : 0;
-      const int r_end_full = (t == 0 && (len & 15u)) ? r1 - (r1 == kRows ? 1 : 0) : r1;
+      const int r_full = base < 0 ? (int)(((uint64_t)(-base) + kTeamThreads - 1) / kTeamThreads) : 0;
+      const int r_end_full = (t == 0 && (len & 15u)) ? r1 - (r1 == kTeamRows ? 1 : 0) : r1;
 
       auto whole = [&](int r) { return aligned && r >= r_full && r < r_end_full; };
       // paged: a lane's chunk offset for the next whole-block row is loaded
@@ -484,7 +518,7 @@ __global__ __launch_bounds__(kThreads) void k_gcm_tiles(GcmArgs a) {
       // starts
       constexpr bool PAGED = GATHER || SCATTER;
       auto chunk_of = [&](int r) -> uint64_t {
-        const uint64_t i0 = (uint64_t)(base + (int64_t)r * kThreads + tid_t);
+        const uint64_t i0 = (uint64_t)(base + (int64_t)r * kTeamThreads + tid_t);
         return a.chunk_off[chunk0 + (i0 >> a.chunk_shift)];
       };
       uint64_t c_next = (PAGED && whole(r_lo)) ? chunk_of(r_lo) : 0;
@@ -501,14 +535,14 @@ __global__ __launch_bounds__(kThreads) void k_gcm_tiles(GcmArgs a) {
         if (fast) {
           // every lane's block index is >= 0 in these rows; pointer arithmetic
           // (not integers) keeps the global address space for the compiler
-          const uint64_t i0 = (uint64_t)(base + (int64_t)r * kThreads + tid_t);
+          const uint64_t i0 = (uint64_t)(base + (int64_t)r * kTeamThreads + tid_t);
           uint8_t* pg = a.pbase + c_cur + ((i0 & cmask) << 4);
           src = GATHER ? pg : a.in + off + 16ull * i0;
           dst = SCATTER ? pg : a.out + off + 16ull * i0;
           v = ld_stream(src);
         }
         uint32_t x0, x1, x2, x3;
-        ctr_rounds12(cc, c0 + (uint32_t)kThreads * (uint32_t)r, x0, x1, x2, x3, rk, tt, L);
+        ctr_rounds12(cc, c0 + (uint32_t)kTeamThreads * (uint32_t)r, x0, x1, x2, x3, rk, tt, L);
         aes_rounds_lds<3>(x0, x1, x2, x3, rk, tt, L);
         u128 x;
         if (fast) {
@@ -517,7 +551,7 @@ __global__ __launch_bounds__(kThreads) void k_gcm_tiles(GcmArgs a) {
           x = OPEN ? u128{{v.x, v.y, v.z, v.w}} : u128{{o.x, o.y, o.z, o.w}};
         } else {
           x = u128_zero();
-          const int64_t i0 = base + (int64_t)r * kThreads + tid_t;
+          const int64_t i0 = base + (int64_t)r * kTeamThreads + tid_t;
           if (i0 >= 0) {
             const uint64_t boff = off + 16ull * (uint64_t)i0;
             const uint64_t rem = len - 16ull * (uint64_t)i0;
@@ -529,100 +563,103 @@ __global__ __launch_bounds__(kThreads) void k_gcm_tiles(GcmArgs a) {
           }
         }
         // The first row's running sum is zero: nothing to multiply.  With 1-4
-        // rows per tile (1024 segments of 16-64 KiB) a seal call went from
+        // KiB rows per tile (1024 segments of 16-64 KiB) a seal call went from
         // 84.2 to 80.4 us; tiles of 128 rows do not notice.
         if (r == r_lo) {
           y = x;
+          if (r + 1 < r1) wave_wait(&ts->mtab, k + 1u);
         } else {
           // GHASH table reads at a priority between the AES issue and combine
-          // phases; the next AES round sets its own
+          // phases; the next AES round sets its own.  One copy per team: the
+          // tables' place goes into the reads' immediate offsets.
           __builtin_amdgcn_s_setprio(1);
-          y = ghash_step_lds(y, x, gt);
+          if (TEAMS == 1 || team == 0u)
+            y = ghash_step_lds(y, x, smem);
+          else
+            y = ghash_step_lds(y, x, smem + kGtabBytes);
         }
       }
     }  // verdict OK
 
-    // Tile partial: lane tid_t contributes y * H^(kThreads + 1 - tid_t), its
+    // Tile end: lane tid_t contributes y * H^(kTeamThreads + 1 - tid_t), its
     // distance from the tile end plus the H^2 that every block's GHASH term
-    // carries.  Wave w = g + kLeaders*i (leader g, i < kFold) needs
-    // H^(64*kLeaders*(kFold - 1 - i)) * H^(64*kLeaders + 1 - 64*g - lane): leader
-    // g folds its waves by Horner in W = H^(64*kLeaders) from the LDS tables,
-    // then multiplies once by the per-lane power.
+    // carries.
     const bool fold = verdict == kVerdictOk;
-    // the wave index is uniform: held in a scalar register, it frees vector
-    // registers across the fold call
-    const uint32_t tid_e = opaque(tid);
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid_e >> 6), lane = tid_e & 63u;
-    u128* stage = (u128*)(smem + kLdsStage);
-    if (tid == kPf0) ti->next_k = claim;
-    // the leaders fetch their lane's power before the barrier, so the load
-    // overlaps the wait for the other waves
+    const uint32_t tid_e = opaque(tid) % kTeamThreads, lane = tid_e & 63u;
+    TileSum* sum = &ts->sum[k % kSlots];
+    if (tw == kRecWave && late) fetch_next(k, lane);
     u128 hp = u128_zero();
-    if (fold && wave < (uint32_t)kLeaders)
-      hp = ld_u128(a.kt.pow_h + (size_t)user * kHPowers + (64u * kLeaders + 1u - 64u * wave - lane));
-    if (fold && wave >= (uint32_t)kLeaders) stage[tid_e - kPf0] = y;
-    __syncthreads();
-    if (wave >= (uint32_t)kLeaders) {
-      prefetch(ti->next_k);  // overlaps the fold
-    } else if (fold) {
-      const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte*)smem;
-      tile_fold(y, lds0 + kLdsStage + 16u * (wave * 64u + lane), lds0 + kLdsFold, hp, lds0 + kLdsRed + 16u * wave,
-                lane);
-    }
-    __syncthreads();
-    // wave 0 finishes the tile (fold, one and the row range are wave-uniform);
-    // lane 0 writes
-    if (wave == 0) {
-      if (fold) {
-        u128 p = red[0];
-        for (int w = 1; w < kLeaders; w++) p = u128_xor(p, red[w]);
-        if (r0 == 0 && r1 == kRows) {
-          if (!one && lane == 0) st_u128(a.partials + g, p);
-        } else {
-          // a piece of a cut tile: its lane powers assumed rows up to the
-          // tile's end, so it still carries H^(kThreads * (kRows - r1));
-          // pieces meet in the tile's (zeroed) partial by XOR
-          if (r1 < kRows) p = gf_mul_wave(p, ld_u128(a.kt.pow_hr + (size_t)user * kRows + (kRows - r1)), lane);
-          if (lane == 0) {
-            uint32_t* dst = (uint32_t*)(a.partials + g);
-            for (int j = 0; j < 4; j++) atomicXor(dst + j, p.w[j]);
-          }
-        }
-        if (one && lane == 0) {
-          // S = P_0 xor H*L, tag = E_K(J0) xor S (the finalize pass skips this segment)
-          const u128 tag = u128_xor(p, red[kLeaders]);
-          if (!OPEN) {
-            uint32_t* to = (uint32_t*)(a.tags_out + 16ull * s);
-            for (int j = 0; j < 4; j++) to[j] = tag.w[j];
-          } else {
-            const uint32_t* tin = (const uint32_t*)(a.tags_in + 16ull * s);
-            uint32_t diff = 0;
-            for (int j = 0; j < 4; j++) diff |= tin[j] ^ tag.w[j];
-            a.verdicts[s] = diff ? kVerdictAuthFail : kVerdictOk;
-            tile_failed = diff != 0u;
-          }
-        }
-      } else if (one && !OPEN && lane == 0) {
-        uint32_t* to = (uint32_t*)(a.tags_out + 16ull * s);  // rejected: zero tag
-        for (int j = 0; j < 4; j++) to[j] = 0u;
+    if (fold) hp = ld_u128(a.kt.pow_h + (size_t)user * kHPowers + (kTeamThreads + 1u - tid_e));
+    wave_wait(&ts->fin, k - (kSlots - 1u));  // the slot's previous tile is finished
+    wave_arrive(&sum->rows);
+    if (tw == kTabWave) {
+      const TileInfo* tn = &ts->info[(k + 1u) % kSlots];
+      wave_wait(&ts->rec, k + 2u);
+      const uint32_t nu = __builtin_amdgcn_readfirstlane(tn->user);
+      if ((uint32_t)__builtin_amdgcn_readfirstlane(tn->g) != kNoTile && nu != user) {
+        const Tables m = read_tables(nu, lane);
+        wave_wait(&sum->rows, kTeamWaves);
+        write_tables(m, lane);
       }
+      wave_set(&ts->mtab, k + 2u);
+    }
+    if (fold) {
+      const u128 z = wave_sum_of(y, hp);
+      if (lane < 4u)
+        atomicXor(&sum->z[lane], lane == 0u ? z.w[0] : lane == 1u ? z.w[1] : lane == 2u ? z.w[2] : z.w[3]);
+    }
+    if (wave_arrive(&sum->done) != kTeamWaves - 1u) continue;
+
+    // the last wave of the team finishes the tile (fold, one and the row range
+    // are wave-uniform); lane 0 writes
+    bool failed = false;
+    if (fold) {
+      u128 p = u128{{sum->z[0], sum->z[1], sum->z[2], sum->z[3]}};
+      if (r0 == 0 && r1 == kTeamRows) {
+        if (!one && lane == 0) st_u128(a.partials + g, p);
+      } else {
+        // a piece of a cut tile: its lane powers assumed rows up to the
+        // tile's end, so it still carries H^(kTeamThreads * (kTeamRows - r1));
+        // pieces meet in the tile's (zeroed) partial by XOR
+        if (r1 < kTeamRows)
+          p = gf_mul_wave(p, ld_u128(a.kt.pow_hr + (size_t)user * kRows + (kTeamRows - r1) / TEAMS), lane);
+        if (lane == 0) {
+          uint32_t* dst = (uint32_t*)(a.partials + g);
+          for (int j = 0; j < 4; j++) atomicXor(dst + j, p.w[j]);
+        }
+      }
+      if (one) {
+        // S = P_0 xor H*L, tag = E_K(J0) xor S (the finalize pass skips this segment)
+        const u128 tag = u128_xor(p, u128{{ti->fin.x, ti->fin.y, ti->fin.z, ti->fin.w}});
+        if (!OPEN) {
+          uint32_t* to = (uint32_t*)(a.tags_out + 16ull * s);
+          if (lane == 0)
+            for (int j = 0; j < 4; j++) to[j] = tag.w[j];
+        } else {
+          const uint32_t* tin = (const uint32_t*)(a.tags_in + 16ull * s);
+          uint32_t diff = 0;
+          for (int j = 0; j < 4; j++) diff |= tin[j] ^ tag.w[j];
+          failed = __builtin_amdgcn_readfirstlane(diff) != 0;
+          if (lane == 0) a.verdicts[s] = failed ? kVerdictAuthFail : kVerdictOk;
+        }
+      }
+    } else if (one && !OPEN && lane == 0) {
+      uint32_t* to = (uint32_t*)(a.tags_out + 16ull * s);  // rejected: zero tag
+      for (int j = 0; j < 4; j++) to[j] = 0u;
     }
     // open of a contiguous tensor: a one-tile segment whose tag failed
-    // releases zeros only.  Its tile is the whole segment, so the workgroup
-    // zeroes it here (multi-tile and cut segments are zeroed by a later pass
-    // once the finalize pass has their verdicts).
-    if (OPEN && !GATHER && !SCATTER && one && fold) {
-      __syncthreads();  // tile_failed is written
-      if (tile_failed) {
-        for (int r = r_lo; r < r1; r++) {
-          const int64_t i0 = base + (int64_t)r * kThreads + tid_e;
-          if (i0 >= 0) {
-            const uint64_t rem = len - 16ull * (uint64_t)i0;
-            store_block(a.out + off + 16ull * (uint64_t)i0, u128_zero(), rem >= 16 ? 16u : (uint32_t)rem, aligned);
-          }
-        }
+    // releases zeros only.  Its tile is the whole segment, so it is zeroed
+    // here, after every wave's rows (multi-tile and cut segments are zeroed by
+    // a later pass once the finalize pass has their verdicts).
+    if (OPEN && !GATHER && !SCATTER && failed) {
+      const uint32_t z = opaque(0u);
+      for (uint64_t i = lane; i < m; i += 64u) {
+        const uint64_t rem = len - 16ull * i;
+        store_block(a.out + off + 16ull * i, u128{{z, z, z, z}}, rem >= 16 ? 16u : (uint32_t)rem, aligned);
       }
     }
+    if (lane < 8u) ((uint32_t*)sum)[lane] = 0u;  // free for tile k + kSlots
+    wave_set(&ts->fin, k + 1u);
   }
 }
 
@@ -1445,18 +1482,17 @@ __global__ __launch_bounds__(256) void k_key_powers(KeyTableDev kt) {
   }
 }
 
-// Nibble tables of M = H^kThreads (gtab) and W = H^(64 * kLeaders)
-// (gtab_fold): entry [q][v] = (v placed at GCM bits 4q..4q+3, MSB first) * M,
-// built from the four products x^(4q+k) * M.
+// Nibble tables of M = H^1024 and H^512 (k_gcm_tiles with one team, with
+// two): entry [q][v] = (v placed at GCM bits 4q..4q+3, MSB first) * M, built
+// from the four products x^(4q+k) * M.
 __global__ __launch_bounds__(256) void k_key_gtab(KeyTableDev kt) {
   const uint64_t idx = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const uint64_t u = idx / 64u;
   const int q = (int)(idx % 32u);
-  const bool fold = (idx % 64u) >= 32u;
+  const uint32_t two = (uint32_t)(idx / 32u) & 1u;
   if (u >= kt.n_users) return;
-  const u128 h = ld_u128((const uint4*)(kt.h + 4ull * u));
-  const u128 mm = gf_pow(h, fold ? (uint64_t)(64 * kLeaders) : (uint64_t)kThreads);
-  uint4* tab = (fold ? kt.gtab_fold : kt.gtab) + u * 512u;
+  const u128 mm = gf_pow(ld_u128((const uint4*)(kt.h + 4ull * u)), two ? (uint64_t)kThreads / 2 : (uint64_t)kThreads);
+  uint4* tab = kt.gtab + (u * 2u + two) * 512u;
   u128 b[4];
   for (int k = 0; k < 4; k++) b[k] = gf_mul(gf_xpow_elem(4 * q + k), mm);
   for (int v = 0; v < 16; v++) {
@@ -1485,19 +1521,24 @@ hipError_t launch_key_setup(const uint8_t* keys_dev, KeyTableDev kt, hipStream_t
 
 
 
-hipError_t launch_gcm_tiles(const GcmArgs& a, int mode, uint32_t grid, hipStream_t s) {
-  if (a.n_ents == 0) return hipSuccess;
-  const uint32_t g = a.n_ents < grid ? a.n_ents : grid;
+template <int TEAMS>
+static hipError_t launch_tiles(const GcmArgs& a, int mode, uint32_t g, hipStream_t s) {
   switch (mode) {
-    case 0: hipLaunchKernelGGL(k_gcm_tiles<0>, dim3(g), dim3(kThreads), 0, s, a); break;
-    case kModeOpen: hipLaunchKernelGGL(k_gcm_tiles<kModeOpen>, dim3(g), dim3(kThreads), 0, s, a); break;
-    case kModeGather: hipLaunchKernelGGL(k_gcm_tiles<kModeGather>, dim3(g), dim3(kThreads), 0, s, a); break;
+    case 0: hipLaunchKernelGGL((k_gcm_tiles<0, TEAMS>), dim3(g), dim3(kThreads), 0, s, a); break;
+    case kModeOpen: hipLaunchKernelGGL((k_gcm_tiles<kModeOpen, TEAMS>), dim3(g), dim3(kThreads), 0, s, a); break;
+    case kModeGather: hipLaunchKernelGGL((k_gcm_tiles<kModeGather, TEAMS>), dim3(g), dim3(kThreads), 0, s, a); break;
     case kModeOpen | kModeScatter:
-      hipLaunchKernelGGL(k_gcm_tiles<kModeOpen | kModeScatter>, dim3(g), dim3(kThreads), 0, s, a);
+      hipLaunchKernelGGL((k_gcm_tiles<kModeOpen | kModeScatter, TEAMS>), dim3(g), dim3(kThreads), 0, s, a);
       break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+
+hipError_t launch_gcm_tiles(const GcmArgs& a, int mode, uint32_t grid, uint32_t teams, hipStream_t s) {
+  if (a.n_ents == 0) return hipSuccess;
+  const uint32_t g = a.n_ents < grid ? a.n_ents : grid;
+  return teams == 2 ? launch_tiles<2>(a, mode, g, s) : launch_tiles<1>(a, mode, g, s);
 }
 
 hipError_t launch_gcm_small(const GcmArgs& a, bool open, hipStream_t s) {
