@@ -141,18 +141,44 @@ __device__ inline void aes256_encrypt_words(const uint32_t* __restrict__ rk, con
 #undef GIFT_SB
 }
 
-// The same cipher with its table passed in (typically a copy in LDS, where
-// per-lane lookups are cheap, unlike the constant segment): te0 as in
-// AesConst, and S(x) is byte 1 of te0[x].
-__device__ inline void aes256_encrypt_tab(const uint32_t* __restrict__ rk, const uint32_t in[4], uint32_t out[4],
-                                          const uint32_t* te0) {
-  uint32_t s0 = in[0] ^ rk[0], s1 = in[1] ^ rk[1], s2 = in[2] ^ rk[2], s3 = in[3] ^ rk[3];
+// A wave-uniform address of memory that no one writes while the kernel runs:
+// its loads are scalar.
+typedef const __attribute__((address_space(4))) uint32_t* uniform_ptr;
+// a value that is the same in every lane, in scalar registers
+__device__ __forceinline__ uint64_t uniform64(uint64_t v) {
+  // (the builtin's result is a signed int)
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)v);
+  return ((uint64_t)hi << 32) | lo;
+}
+__device__ __forceinline__ uniform_ptr to_uniform(const uint32_t* p) { return (uniform_ptr)uniform64((uint64_t)p); }
+
+// v, which every lane of the wave holds from here on: lane_word reads it from
+// lanes that a branch has switched off, and the compiler, which does not know
+// that, must not move v's load into the branch.
+__device__ __forceinline__ uint32_t held(uint32_t v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+__device__ __forceinline__ uint32_t lane_word(uint32_t v, int lane) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
+}
+
+// The same cipher under wave-uniform round keys, with its table passed in
+// (typically a copy in LDS, where per-lane lookups are cheap, unlike the
+// constant segment): te0 as in AesConst, and S(x) is byte 1 of te0[x].  Lane l
+// of the wave holds round-key word l in rkv: one coalesced load, whose latency
+// comes before the rounds, instead of a load of each round's keys inside them.
+__device__ inline void aes256_encrypt_tab(uint32_t rkv, const uint32_t in[4], uint32_t out[4], const uint32_t* te0) {
+  uint32_t s0 = in[0] ^ lane_word(rkv, 0), s1 = in[1] ^ lane_word(rkv, 1), s2 = in[2] ^ lane_word(rkv, 2),
+           s3 = in[3] ^ lane_word(rkv, 3);
 #define GIFT_TE(w, k) rotl32(te0[((w) >> (8 * (k))) & 0xffu], 8 * (k))
+#pragma unroll 1
   for (int r = 1; r < 14; r++) {
-    const uint32_t t0 = GIFT_TE(s0, 0) ^ GIFT_TE(s1, 1) ^ GIFT_TE(s2, 2) ^ GIFT_TE(s3, 3) ^ rk[4 * r + 0];
-    const uint32_t t1 = GIFT_TE(s1, 0) ^ GIFT_TE(s2, 1) ^ GIFT_TE(s3, 2) ^ GIFT_TE(s0, 3) ^ rk[4 * r + 1];
-    const uint32_t t2 = GIFT_TE(s2, 0) ^ GIFT_TE(s3, 1) ^ GIFT_TE(s0, 2) ^ GIFT_TE(s1, 3) ^ rk[4 * r + 2];
-    const uint32_t t3 = GIFT_TE(s3, 0) ^ GIFT_TE(s0, 1) ^ GIFT_TE(s1, 2) ^ GIFT_TE(s2, 3) ^ rk[4 * r + 3];
+    const uint32_t t0 = GIFT_TE(s0, 0) ^ GIFT_TE(s1, 1) ^ GIFT_TE(s2, 2) ^ GIFT_TE(s3, 3) ^ lane_word(rkv, 4 * r);
+    const uint32_t t1 = GIFT_TE(s1, 0) ^ GIFT_TE(s2, 1) ^ GIFT_TE(s3, 2) ^ GIFT_TE(s0, 3) ^ lane_word(rkv, 4 * r + 1);
+    const uint32_t t2 = GIFT_TE(s2, 0) ^ GIFT_TE(s3, 1) ^ GIFT_TE(s0, 2) ^ GIFT_TE(s1, 3) ^ lane_word(rkv, 4 * r + 2);
+    const uint32_t t3 = GIFT_TE(s3, 0) ^ GIFT_TE(s0, 1) ^ GIFT_TE(s1, 2) ^ GIFT_TE(s2, 3) ^ lane_word(rkv, 4 * r + 3);
     s0 = t0;
     s1 = t1;
     s2 = t2;
@@ -160,23 +186,26 @@ __device__ inline void aes256_encrypt_tab(const uint32_t* __restrict__ rk, const
   }
 #undef GIFT_TE
 #define GIFT_SB(w, k) (((te0[((w) >> (8 * (k))) & 0xffu] >> 8) & 0xffu) << (8 * (k)))
-  out[0] = (GIFT_SB(s0, 0) | GIFT_SB(s1, 1) | GIFT_SB(s2, 2) | GIFT_SB(s3, 3)) ^ rk[56];
-  out[1] = (GIFT_SB(s1, 0) | GIFT_SB(s2, 1) | GIFT_SB(s3, 2) | GIFT_SB(s0, 3)) ^ rk[57];
-  out[2] = (GIFT_SB(s2, 0) | GIFT_SB(s3, 1) | GIFT_SB(s0, 2) | GIFT_SB(s1, 3)) ^ rk[58];
-  out[3] = (GIFT_SB(s3, 0) | GIFT_SB(s0, 1) | GIFT_SB(s1, 2) | GIFT_SB(s2, 3)) ^ rk[59];
+  out[0] = (GIFT_SB(s0, 0) | GIFT_SB(s1, 1) | GIFT_SB(s2, 2) | GIFT_SB(s3, 3)) ^ lane_word(rkv, 56);
+  out[1] = (GIFT_SB(s1, 0) | GIFT_SB(s2, 1) | GIFT_SB(s3, 2) | GIFT_SB(s0, 3)) ^ lane_word(rkv, 57);
+  out[2] = (GIFT_SB(s2, 0) | GIFT_SB(s3, 1) | GIFT_SB(s0, 2) | GIFT_SB(s1, 3)) ^ lane_word(rkv, 58);
+  out[3] = (GIFT_SB(s3, 0) | GIFT_SB(s0, 1) | GIFT_SB(s1, 2) | GIFT_SB(s2, 3)) ^ lane_word(rkv, 59);
 #undef GIFT_SB
 }
 
-// Equivalent inverse cipher with td0 and the inverse S-box passed in.
-__device__ inline void aes256_decrypt_tab(const uint32_t* __restrict__ dk, const uint32_t in[4], uint32_t out[4],
-                                          const uint32_t* td0, const uint8_t* isb) {
-  uint32_t s0 = in[0] ^ dk[56], s1 = in[1] ^ dk[57], s2 = in[2] ^ dk[58], s3 = in[3] ^ dk[59];
+// Equivalent inverse cipher with td0 and the inverse S-box passed in; lane l of
+// the wave holds word l of its round keys in dkv.
+__device__ inline void aes256_decrypt_tab(uint32_t dkv, const uint32_t in[4], uint32_t out[4], const uint32_t* td0,
+                                          const uint8_t* isb) {
+  uint32_t s0 = in[0] ^ lane_word(dkv, 56), s1 = in[1] ^ lane_word(dkv, 57), s2 = in[2] ^ lane_word(dkv, 58),
+           s3 = in[3] ^ lane_word(dkv, 59);
 #define GIFT_TD(w, k) rotl32(td0[((w) >> (8 * (k))) & 0xffu], 8 * (k))
+#pragma unroll 1
   for (int r = 13; r >= 1; r--) {
-    const uint32_t t0 = GIFT_TD(s0, 0) ^ GIFT_TD(s3, 1) ^ GIFT_TD(s2, 2) ^ GIFT_TD(s1, 3) ^ dk[4 * r + 0];
-    const uint32_t t1 = GIFT_TD(s1, 0) ^ GIFT_TD(s0, 1) ^ GIFT_TD(s3, 2) ^ GIFT_TD(s2, 3) ^ dk[4 * r + 1];
-    const uint32_t t2 = GIFT_TD(s2, 0) ^ GIFT_TD(s1, 1) ^ GIFT_TD(s0, 2) ^ GIFT_TD(s3, 3) ^ dk[4 * r + 2];
-    const uint32_t t3 = GIFT_TD(s3, 0) ^ GIFT_TD(s2, 1) ^ GIFT_TD(s1, 2) ^ GIFT_TD(s0, 3) ^ dk[4 * r + 3];
+    const uint32_t t0 = GIFT_TD(s0, 0) ^ GIFT_TD(s3, 1) ^ GIFT_TD(s2, 2) ^ GIFT_TD(s1, 3) ^ lane_word(dkv, 4 * r);
+    const uint32_t t1 = GIFT_TD(s1, 0) ^ GIFT_TD(s0, 1) ^ GIFT_TD(s3, 2) ^ GIFT_TD(s2, 3) ^ lane_word(dkv, 4 * r + 1);
+    const uint32_t t2 = GIFT_TD(s2, 0) ^ GIFT_TD(s1, 1) ^ GIFT_TD(s0, 2) ^ GIFT_TD(s3, 3) ^ lane_word(dkv, 4 * r + 2);
+    const uint32_t t3 = GIFT_TD(s3, 0) ^ GIFT_TD(s2, 1) ^ GIFT_TD(s1, 2) ^ GIFT_TD(s0, 3) ^ lane_word(dkv, 4 * r + 3);
     s0 = t0;
     s1 = t1;
     s2 = t2;
@@ -184,10 +213,10 @@ __device__ inline void aes256_decrypt_tab(const uint32_t* __restrict__ dk, const
   }
 #undef GIFT_TD
 #define GIFT_ISB(w, k) ((uint32_t)isb[((w) >> (8 * (k))) & 0xffu] << (8 * (k)))
-  out[0] = (GIFT_ISB(s0, 0) | GIFT_ISB(s3, 1) | GIFT_ISB(s2, 2) | GIFT_ISB(s1, 3)) ^ dk[0];
-  out[1] = (GIFT_ISB(s1, 0) | GIFT_ISB(s0, 1) | GIFT_ISB(s3, 2) | GIFT_ISB(s2, 3)) ^ dk[1];
-  out[2] = (GIFT_ISB(s2, 0) | GIFT_ISB(s1, 1) | GIFT_ISB(s0, 2) | GIFT_ISB(s3, 3)) ^ dk[2];
-  out[3] = (GIFT_ISB(s3, 0) | GIFT_ISB(s2, 1) | GIFT_ISB(s1, 2) | GIFT_ISB(s0, 3)) ^ dk[3];
+  out[0] = (GIFT_ISB(s0, 0) | GIFT_ISB(s3, 1) | GIFT_ISB(s2, 2) | GIFT_ISB(s1, 3)) ^ lane_word(dkv, 0);
+  out[1] = (GIFT_ISB(s1, 0) | GIFT_ISB(s0, 1) | GIFT_ISB(s3, 2) | GIFT_ISB(s2, 3)) ^ lane_word(dkv, 1);
+  out[2] = (GIFT_ISB(s2, 0) | GIFT_ISB(s1, 1) | GIFT_ISB(s0, 2) | GIFT_ISB(s3, 3)) ^ lane_word(dkv, 2);
+  out[3] = (GIFT_ISB(s3, 0) | GIFT_ISB(s2, 1) | GIFT_ISB(s1, 2) | GIFT_ISB(s0, 3)) ^ lane_word(dkv, 3);
 #undef GIFT_ISB
 }
 
@@ -330,15 +359,12 @@ __device__ __forceinline__ uint32_t wave_xor(uint32_t v) {
          (uint32_t)__builtin_amdgcn_readlane((int)v, 32) ^ (uint32_t)__builtin_amdgcn_readlane((int)v, 48);
 }
 
-// The same product computed by a whole wave, x and y wave-uniform, returned
-// wave-uniform: lane n < 16 takes byte n of x, i.e. the sum over j < 8 of
-// x_(8n+j) * y * x^(8n+j), starting from y * x^(8n) (n shifts by 8, each
-// folding the pushed-out byte back as in gf_mul), and the 16 partial sums are
-// XORed across the lanes' row.  About a quarter of gf_mul's instructions in
-// the wave's critical path.  Every lane of the wave must be active.
-__device__ inline u128 gf_mul_wave(const u128& x, const u128& y, uint32_t lane) {
+// Byte n of x times y, that is the sum over j < 8 of x_(8n+j) * y * x^(8n+j):
+// the share of a product that lane n of 16 computes (n < 16; the 16 shares XOR
+// to x * y).  It starts from y * x^(8n), n shifts by 8, each folding the
+// pushed-out byte back as in gf_mul.
+__device__ inline u128 gf_mul_slice(const u128& x, const u128& y, uint32_t n) {
   uint32_t v0 = bswap32(y.w[0]), v1 = bswap32(y.w[1]), v2 = bswap32(y.w[2]), v3 = bswap32(y.w[3]);
-  const uint32_t n = lane & 15u;
 #pragma unroll 1
   for (uint32_t k = 0; k < n; k++) {
     const uint32_t t = v3 & 0xFFu;
@@ -350,7 +376,7 @@ __device__ inline u128 gf_mul_wave(const u128& x, const u128& y, uint32_t lane) 
   // byte n of x, by shifts of its two halves (an index into x.w would go
   // through private memory)
   const uint64_t lo = ((uint64_t)x.w[1] << 32) | x.w[0], hi = ((uint64_t)x.w[3] << 32) | x.w[2];
-  const uint32_t xb = lane < 16u ? (uint32_t)(((n & 8u) ? hi : lo) >> (8u * (n & 7u))) & 0xFFu : 0u;
+  const uint32_t xb = (uint32_t)(((n & 8u) ? hi : lo) >> (8u * (n & 7u))) & 0xFFu;
   uint32_t z0 = 0, z1 = 0, z2 = 0, z3 = 0;
 #pragma unroll
   for (int j = 0; j < 8; j++) {
@@ -367,7 +393,18 @@ __device__ inline u128 gf_mul_wave(const u128& x, const u128& y, uint32_t lane) 
       v0 = (v0 >> 1) ^ (0xE1000000u & carry);
     }
   }
-  return u128{{bswap32(wave_xor(z0)), bswap32(wave_xor(z1)), bswap32(wave_xor(z2)), bswap32(wave_xor(z3))}};
+  return u128{{bswap32(z0), bswap32(z1), bswap32(z2), bswap32(z3)}};
+}
+
+// The same product computed by a whole wave, x and y wave-uniform, returned
+// wave-uniform: 16 lanes take a byte of x each.  About a quarter of gf_mul's
+// instructions in the wave's critical path.  Every lane of the wave must be
+// active.
+__device__ inline u128 gf_mul_wave(const u128& x, const u128& y, uint32_t lane) {
+  u128 z = gf_mul_slice(x, y, lane & 15u);
+#pragma unroll
+  for (int j = 0; j < 4; j++) z.w[j] = wave_xor(lane < 16u ? z.w[j] : 0u);
+  return z;
 }
 
 }  // namespace gift

@@ -92,10 +92,11 @@ TilePlan plan_tiles(uint32_t n_tiles, uint64_t tile_rows_all, uint32_t n_multi, 
   // A row takes a team about 5 us, the finalize pass about 5 us of stream time
   // and, on open, the zeroing pass behind it 4 us more, so a cut that shortens
   // the longest tile by fewer than two rows (three on open) does not pay.
-  // With one worker no tile of up to kPieceRows rows is cut.
+  // With one worker no tile of up to kPieceRows rows is cut (and the queue is
+  // as long as the tiles, with nothing to pad).
   const uint64_t p = (tile_rows_all + t.workers - 1) / t.workers;
-  if (n_multi == 0 && n_tiles < t.workers && one_rows_max <= (uint32_t)kPieceRows &&
-      one_rows_max < p + (open ? 3u : 2u))
+  if (n_multi == 0 && one_rows_max <= (uint32_t)kPieceRows &&
+      (n_tiles >= t.workers || one_rows_max < p + (open ? 3u : 2u)))
     t.workers = 1;
   t.q = plan_queue(n_tiles, tile_rows_all, n_multi, one_rows_max, t.workers);
   t.grid = std::min(cus, std::max(t.q.grid, n_tiles));
@@ -810,6 +811,7 @@ gift_status run_gcm(const gift_tensor* t, const gift_segment_table* st, gift_key
       a.tile_order = (const TileEnt*)(scratch + o_to);
       a.seg_cut = (const uint32_t*)(scratch + o_sc);
       a.tile_counter = (uint32_t*)(scratch + o_qh);
+      a.any_failed = a.tile_counter + 1;
       a.verdicts = verdicts;
       a.tags_out = tags_out;
       a.tags_in = tags_in;
@@ -840,7 +842,7 @@ gift_status run_gcm(const gift_tensor* t, const gift_segment_table* st, gift_key
       // its own failed segments (the small-segment kernel, or the tile kernel
       // for an uncut one-tile segment)
       if (e == hipSuccess && OPEN && Q.finalize)
-        e = launch_zero_failed(d_desc, n, a.tile_base, P.n_tiles, verdicts, nullptr, (uint8_t*)out, 0u, cus * 4u,
+        e = launch_zero_failed(a.any_failed, d_desc, n, a.tile_base, P.n_tiles, verdicts, nullptr, (uint8_t*)out, 0u, cus,
                                stream);
       if (e != hipSuccess) {
         rs = hip_fail(e, "gcm launch");
@@ -860,9 +862,9 @@ gift_status run_gcm(const gift_tensor* t, const gift_segment_table* st, gift_key
   e = sg->upload(
       scratch, host.data(), o_st, stream,
       [&](const void* src) {
-        hipError_t r = launch_prologue(scratch, src, o_st, n, kNoBids, st->row_labels, n ? verdicts : nullptr,
+        hipError_t r = launch_prologue(scratch, src, o_st, n, t->n_rows, kNoBids, st->row_labels, n ? verdicts : nullptr,
                                        &kt->dev, (uint4*)(scratch + o_fn), (uint4*)(scratch + o_pt), P.n_tiles, o_br,
-                                       n ? &ex : nullptr, stream);
+                                       n ? &ex : nullptr, nullptr, stream);
         if (r != hipSuccess) {
           rs = hip_fail(r, "prologue launch");
           return r;
@@ -1051,17 +1053,11 @@ gift_status run_paged(const gift_paged_kv* kv, const gift_request* reqs, uint32_
   gift_status rs = GIFT_OK;
   EventMark call_ev;  // the event recorded behind the call's last kernel
   const SegDesc* d_desc = (const SegDesc*)(scratch + o_desc);
-  const uint32_t* d_bid = (const uint32_t*)(scratch + o_bid);
   uint64_t* d_ck = (uint64_t*)(scratch + o_ck);
+  const ChunkTable chunks{d_ck, cpos, per_block_chunks, kv->layer_stride, kv->block_stride, kv->part_stride, kv->n_parts};
   // the call's kernels after the prologue, enqueued while the staging slot is
   // held (one event behind the last of them frees the slot)
   auto rest = [&]() -> hipError_t {
-    e = launch_chunk_table(d_desc, n, d_bid, kv->n_layers, kv->n_parts, kv->layer_stride, kv->block_stride,
-                           kv->part_stride, d_ck, stream);
-    if (e != hipSuccess) {
-      rs = hip_fail(e, "paged expansion");
-      return e;
-    }
     GcmArgs a{};  // zero-initialised: no field is left undefined
     a.in = (const uint8_t*)in;
     a.out = (uint8_t*)out;
@@ -1081,6 +1077,7 @@ gift_status run_paged(const gift_paged_kv* kv, const gift_request* reqs, uint32_
     a.tile_order = (const TileEnt*)(scratch + o_to);
     a.seg_cut = (const uint32_t*)(scratch + o_sc);
     a.tile_counter = (uint32_t*)(scratch + o_qh);
+    a.any_failed = a.tile_counter + 1;
     a.verdicts = verdicts;
     a.tags_out = tags_out;
     a.tags_in = tags_in;
@@ -1096,8 +1093,8 @@ gift_status run_paged(const gift_paged_kv* kv, const gift_request* reqs, uint32_
     if (e == hipSuccess && g_prof_after) e = hipEventRecord(g_prof_after, stream);
     if (e == hipSuccess) e = launch_gcm_finalize(a, OPEN, stream);
     if (e == hipSuccess && OPEN)
-      e = launch_zero_failed(d_desc, n, (const uint32_t*)(scratch + o_tb), n_tiles, verdicts, d_ck,
-                             (uint8_t*)kv->base, shift, cus * 4u, stream);
+      e = launch_zero_failed(a.any_failed, d_desc, n, (const uint32_t*)(scratch + o_tb), n_tiles, verdicts, d_ck,
+                             (uint8_t*)kv->base, shift, cus, stream);
     if (e != hipSuccess) {
       rs = hip_fail(e, "paged gcm launch");
       return e;
@@ -1106,9 +1103,9 @@ gift_status run_paged(const gift_paged_kv* kv, const gift_request* reqs, uint32_
   };
   e = sg ? sg->upload(scratch, host.data(), o_st, stream,
                       [&](const void* src) {
-                        hipError_t r = launch_prologue(scratch, src, o_st, n, o_bid, labels, verdicts, &kt->dev,
+                        hipError_t r = launch_prologue(scratch, src, o_st, n, total_bids, o_bid, labels, verdicts, &kt->dev,
                                                        (uint4*)(scratch + o_fn), (uint4*)(scratch + o_pt), n_tiles,
-                                                       o_br, &ex, stream);
+                                                       o_br, &ex, &chunks, stream);
                         if (r != hipSuccess) {
                           rs = hip_fail(r, "prologue launch");
                           return r;
@@ -1290,8 +1287,8 @@ gift_status gift_check_owner(const gift_segment_table* st, const uint32_t* label
   EventMark call_ev;  // the event recorded behind the prologue
   e = sg ? sg->upload(d, P.descs.data(), bytes, stream,
                       [&](const void* src) {
-                        return launch_prologue(d, src, bytes, n, kNoBids, labels, st->verdicts, nullptr, nullptr,
-                                               nullptr, 0u, 0u, nullptr, stream);
+                        return launch_prologue(d, src, bytes, n, n_rows, kNoBids, labels, st->verdicts, nullptr, nullptr,
+                                               nullptr, 0u, 0u, nullptr, nullptr, stream);
                       },
                       false, &call_ev)
          : hipErrorInvalidDevice;
@@ -1366,8 +1363,8 @@ static gift_status run_tokens(bool decrypt, const gift_segment_table* st, uint64
     Staging* sg = staging_for(dev);
     e = sg ? sg->upload(d, host.data(), staged, stream,
                         [&](const void* src) {
-                          hipError_t r = launch_prologue(d, src, staged, n, kNoBids, nullptr, nullptr, nullptr,
-                                                         nullptr, nullptr, 0u, 0u, nullptr, stream);
+                          hipError_t r = launch_prologue(d, src, staged, n, 0, kNoBids, nullptr, nullptr, nullptr,
+                                                         nullptr, nullptr, 0u, 0u, nullptr, nullptr, stream);
                           return r != hipSuccess ? r : rest();
                         },
                         false, &call_ev)

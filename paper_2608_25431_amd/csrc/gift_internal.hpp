@@ -105,10 +105,11 @@ struct GcmArgs {
   uint32_t n_small;
   uint32_t n_multi;            // nonzero: launch the finalize pass (some segment may have more than one entry)
   uint4* partials;             // [n_tiles] GHASH partial of each tile
-  const uint4* fin;            // [n_segs] E_K(J0) xor H*L of one-tile segments (from the prologue)
+  const uint4* fin;            // [n_segs] E_K(J0) xor H*L of tiled segments (from the prologue)
   const TileEnt* tile_order;   // [n_ents] tiles and pieces in the order the workgroups claim them
   const uint32_t* seg_cut;     // [n_segs] 1: a one-tile segment cut into pieces (the finalize pass forms its tag)
   uint32_t* tile_counter;      // work-queue head, zeroed with the staged tables
+  uint32_t* any_failed;        // open: set when a tag failed and the zeroing pass has work; zeroed with the tables
   int32_t* verdicts;           // [n_segs]
   uint8_t* tags_out;           // seal: [n_segs][16]
   const uint8_t* tags_in;      // open: [n_segs][16]
@@ -172,14 +173,25 @@ struct ExpandArgs {
 // and, when verdicts is not NULL, writes each segment's first verdict: the
 // owner check against labels (indexed by row, or by the block ids at byte
 // bids_off of the tables for paged calls) or OK without labels.  With a key
-// table it also writes fin[s] = E_K(J0) xor H*L of every one-tile segment s.
-// The descriptors sit at byte 0 of the tables.  With ex, one workgroup runs
+// table it also writes fin[s] = E_K(J0) xor H*L of every tiled segment s.
+// The descriptors sit at byte 0 of the tables; rows: the rows of all segments
+// that the owner check reads.  With ex, one workgroup runs
 // the segment-table expansion into *ex meanwhile, from the brief records at
 // byte brief_off of the tables.
 constexpr uint64_t kNoBids = ~0ull;
-hipError_t launch_prologue(void* dst, const void* src, size_t bytes, uint32_t n_segs, uint64_t bids_off,
+// Paged calls: with chunks, the prologue also writes the offset in the cache of
+// each of the n chunks, in the order of the block-id array (per_block chunks,
+// layer by layer and part by part, for each block id).
+struct ChunkTable {
+  uint64_t* off;
+  uint64_t n, per_block;
+  uint64_t layer_stride, block_stride, part_stride;
+  uint32_t parts;
+};
+hipError_t launch_prologue(void* dst, const void* src, size_t bytes, uint32_t n_segs, uint64_t rows, uint64_t bids_off,
                            const uint32_t* labels, int32_t* verdicts, const KeyTableDev* kt, uint4* fin,
-                           uint4* zero, uint32_t n_zero, uint64_t brief_off, const ExpandArgs* ex, hipStream_t s);
+                           uint4* zero, uint32_t n_zero, uint64_t brief_off, const ExpandArgs* ex,
+                           const ChunkTable* chunks, hipStream_t s);
 // The expansion alone, on brief records in device memory: the library's test
 // hook.
 hipError_t launch_expand(const SegBrief* brief, uint32_t n_segs, const ExpandArgs& x, hipStream_t s);
@@ -197,15 +209,11 @@ hipError_t launch_gcm_finalize(const GcmArgs& a, bool open, hipStream_t s);
 hipError_t launch_zero_ranges(uint8_t* out, const ZeroRange* r, uint32_t n, const int32_t* verdicts, uint32_t grid,
                               hipStream_t s);
 hipError_t launch_wipe(void* p, size_t bytes, hipStream_t s);
-// Paged calls: chunk offsets from the block tables (segment rows index bids).
-hipError_t launch_chunk_table(const SegDesc* segs, uint32_t n_segs, const uint32_t* bids, uint32_t n_layers,
-                              uint32_t n_parts, uint64_t layer_stride, uint64_t block_stride, uint64_t part_stride,
-                              uint64_t* chunk_off, hipStream_t s);
 // Open: zeroes the output of failed segments tile by tile -- contiguous
 // (chunk_off NULL, base = out): every segment whose verdict is not OK;
 // through block tables (base = the cache): requests whose verdict is
 // AUTH_FAIL only (a request rejected by the label check writes nothing).
-hipError_t launch_zero_failed(const SegDesc* segs, uint32_t n_segs, const uint32_t* tile_base, uint32_t n_tiles,
+hipError_t launch_zero_failed(const uint32_t* any_failed, const SegDesc* segs, uint32_t n_segs, const uint32_t* tile_base, uint32_t n_tiles,
                               const int32_t* verdicts, const uint64_t* chunk_off, uint8_t* base, uint32_t chunk_shift,
                               uint32_t grid, hipStream_t s);
 // Per-token block encryption (decrypt == true: the inverse).  Rows of the

@@ -81,12 +81,16 @@ struct Team {
   static_assert(lds_bytes <= 160u * 1024u, "LDS of a gfx950 workgroup");
 };
 
-// a value that is the same in every lane, in scalar registers
-__device__ __forceinline__ uint64_t uniform64(uint64_t v) {
-  // (the builtin's result is a signed int)
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)v);
-  return ((uint64_t)hi << 32) | lo;
+// A segment's descriptor by scalar loads, s wave-uniform.
+__device__ __forceinline__ SegDesc ld_uniform(const SegDesc* p) {
+  union {
+    uint32_t w[sizeof(SegDesc) / 4];
+    SegDesc d;
+  } u;
+  const uniform_ptr q = to_uniform((const uint32_t*)p);
+#pragma unroll
+  for (uint32_t i = 0; i < sizeof(SegDesc) / 4; i++) u.w[i] = q[i];
+  return u.d;
 }
 
 // Counters in LDS between the waves of one workgroup, which are all resident
@@ -268,26 +272,42 @@ __device__ __forceinline__ u128 ghash_step_lds(const u128& y, const u128& x, con
   return u128{{a0, a1, a2, a3}};
 }
 
-__device__ __forceinline__ u128 load_block(const uint8_t* p, uint32_t n, bool aligned) {
-  if (aligned && n == 16) {
-    uint4 v = *(const uint4*)p;
+// The first n (1..16) bytes of a block at any address.  Global loads and
+// stores of any width may be unaligned on gfx950, so a whole block is one
+// 16-byte access and a partial one up to four (8, 4, 2, 1 bytes).
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef u32x4 u32x4_any __attribute__((aligned(1)));
+typedef uint64_t u64_any __attribute__((aligned(1)));
+typedef uint32_t u32_any __attribute__((aligned(1)));
+typedef uint16_t u16_any __attribute__((aligned(1)));
+__device__ __forceinline__ u128 load_block(const uint8_t* p, uint32_t n) {
+  if (n == 16) {
+    const u32x4 v = *(const u32x4_any*)p;
     return u128{{v.x, v.y, v.z, v.w}};
   }
-  u128 r = u128_zero();
-#pragma unroll
-  for (uint32_t k = 0; k < 16; k++)
-    if (k < n) r.w[k >> 2] |= (uint32_t)p[k] << (8 * (k & 3));
-  return r;
+  const uint32_t hi = n & 8u;
+  uint64_t v = 0;
+  uint32_t w = 0, t = 0;  // the 4 bytes after those (or at the start), then the last up to 3
+  if (hi) v = *(const u64_any*)p;
+  if (n & 4u) w = *(const u32_any*)(p + hi);
+  if (n & 2u) t = *(const u16_any*)(p + (n & 12u));
+  if (n & 1u) t |= (uint32_t)p[n & 14u] << (8u * (n & 2u));
+  const uint32_t a = (n & 4u) ? w : t, b = (n & 4u) ? t : 0u;
+  return u128{{hi ? (uint32_t)v : a, hi ? (uint32_t)(v >> 32) : b, hi ? a : 0u, hi ? b : 0u}};
 }
 
-__device__ __forceinline__ void store_block(uint8_t* p, const u128& v, uint32_t n, bool aligned) {
-  if (aligned && n == 16) {
-    *(uint4*)p = make_uint4(v.w[0], v.w[1], v.w[2], v.w[3]);
+__device__ __forceinline__ void store_block(uint8_t* p, const u128& v, uint32_t n) {
+  if (n == 16) {
+    *(u32x4_any*)p = u32x4{v.w[0], v.w[1], v.w[2], v.w[3]};
     return;
   }
-#pragma unroll
-  for (uint32_t k = 0; k < 16; k++)
-    if (k < n) p[k] = (uint8_t)(v.w[k >> 2] >> (8 * (k & 3)));
+  const uint32_t v0 = v.w[0], v1 = v.w[1], v2 = v.w[2], v3 = v.w[3];
+  const uint32_t hi = n & 8u, w = hi ? v2 : v0, w1 = hi ? v3 : v1;
+  const uint32_t t = (n & 4u) ? w1 : w;
+  if (hi) *(u64_any*)p = ((uint64_t)v1 << 32) | v0;
+  if (n & 4u) *(u32_any*)(p + hi) = w;
+  if (n & 2u) *(u16_any*)(p + (n & 12u)) = (uint16_t)t;
+  if (n & 1u) p[n & 14u] = (uint8_t)(t >> (8u * (n & 2u)));
 }
 
 // keep the first n bytes of a block, zero the rest
@@ -306,14 +326,13 @@ __device__ __forceinline__ u128 mask_block(const u128& v, uint32_t n) {
 // Whole-block stream of the per-block kernel: every plaintext and ciphertext
 // block passes through the caches once, so its 16-byte load and store carry
 // the non-temporal hint.  Measured on llama3_8b_kv: seal kernel -0.75%.
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ uint4 ld_stream(const uint8_t* p) {
-  const u32x4 t = __builtin_nontemporal_load((const u32x4*)p);
+  const u32x4 t = __builtin_nontemporal_load((const u32x4_any*)p);
   return make_uint4(t.x, t.y, t.z, t.w);
 }
 __device__ __forceinline__ void st_stream(uint8_t* p, const uint4& v) {
   const u32x4 t = {v.x, v.y, v.z, v.w};
-  __builtin_nontemporal_store(t, (u32x4*)p);
+  __builtin_nontemporal_store(t, (u32x4_any*)p);
 }
 
 __device__ __forceinline__ u128 ld_u128(const uint4* p) {
@@ -461,7 +480,6 @@ __global__ __launch_bounds__(kThreads) void k_gcm_tiles(GcmArgs a) {
     const uint32_t m = __builtin_amdgcn_readfirstlane(ti->desc.nblocks);
     const uint64_t off = uniform64(ti->desc.byte_off), len = uniform64(ti->desc.len);
     const uint32_t flags = __builtin_amdgcn_readfirstlane(ti->desc.flags);
-    const bool aligned = (flags & kSegAligned) != 0;
     // a one-tile segment whose tile is cut into pieces gets its tag from the finalize pass
     const bool one = (flags & kSegOneTile) != 0 && r0 == 0 && r1 == kTeamRows;
     const int64_t base = (int64_t)m - (int64_t)(t + 1) * (int64_t)kTileBlocks;  // block index of virtual slot 0
@@ -498,7 +516,7 @@ __global__ __launch_bounds__(kThreads) void k_gcm_tiles(GcmArgs a) {
           const int64_t i0 = base + (int64_t)r * kTeamThreads + tid_t;
           if (i0 >= 0) {
             const uint64_t rem = len - 16ull * (uint64_t)i0;
-            store_block(a.out + off + 16ull * (uint64_t)i0, u128{{z, z, z, z}}, rem >= 16 ? 16u : (uint32_t)rem, aligned);
+            store_block(a.out + off + 16ull * (uint64_t)i0, u128{{z, z, z, z}}, rem >= 16 ? 16u : (uint32_t)rem);
           }
         }
       }
@@ -507,12 +525,13 @@ __global__ __launch_bounds__(kThreads) void k_gcm_tiles(GcmArgs a) {
       const uint32_t c0 = 2u + (uint32_t)(base + (int64_t)tid_t);  // counter of this lane in row 0, mod 2^32
       ctr_cache_init(cc, k0, k1, k2, c0, rk, tt, L);
 
-      // rows where every lane holds a whole block and the segment is 16-byte
-      // aligned take the branch-free path
+      // Rows where every lane holds a whole block take the branch-free path,
+      // whatever the segment's alignment (256 prompts of int32 tokens, most of
+      // them unaligned: kernel 27.8 -> 21.9 us against byte loads and stores).
       const int r_full = base < 0 ? (int)(((uint64_t)(-base) + kTeamThreads - 1) / kTeamThreads) : 0;
       const int r_end_full = (t == 0 && (len & 15u)) ? r1 - (r1 == kTeamRows ? 1 : 0) : r1;
 
-      auto whole = [&](int r) { return aligned && r >= r_full && r < r_end_full; };
+      auto whole = [&](int r) { return r >= r_full && r < r_end_full; };
       // paged: a lane's chunk offset for the next whole-block row is loaded
       // one row ahead, so the gather or scatter address is ready when the row
       // starts
@@ -556,9 +575,9 @@ __global__ __launch_bounds__(kThreads) void k_gcm_tiles(GcmArgs a) {
             const uint64_t boff = off + 16ull * (uint64_t)i0;
             const uint64_t rem = len - 16ull * (uint64_t)i0;
             const uint32_t n = rem >= 16 ? 16u : (uint32_t)rem;
-            const u128 in = load_block(GATHER ? paged((uint64_t)i0) : a.in + boff, n, aligned);
+            const u128 in = load_block(GATHER ? paged((uint64_t)i0) : a.in + boff, n);
             const u128 o = mask_block(u128{{in.w[0] ^ x0, in.w[1] ^ x1, in.w[2] ^ x2, in.w[3] ^ x3}}, n);
-            store_block(SCATTER ? paged((uint64_t)i0) : a.out + boff, o, n, aligned);
+            store_block(SCATTER ? paged((uint64_t)i0) : a.out + boff, o, n);
             x = OPEN ? in : o;
           }
         }
@@ -641,6 +660,7 @@ __global__ __launch_bounds__(kThreads) void k_gcm_tiles(GcmArgs a) {
           for (int j = 0; j < 4; j++) diff |= tin[j] ^ tag.w[j];
           failed = __builtin_amdgcn_readfirstlane(diff) != 0;
           if (lane == 0) a.verdicts[s] = failed ? kVerdictAuthFail : kVerdictOk;
+          if (SCATTER && failed && lane == 0) *a.any_failed = 1u;
         }
       }
     } else if (one && !OPEN && lane == 0) {
@@ -655,7 +675,7 @@ __global__ __launch_bounds__(kThreads) void k_gcm_tiles(GcmArgs a) {
       const uint32_t z = opaque(0u);
       for (uint64_t i = lane; i < m; i += 64u) {
         const uint64_t rem = len - 16ull * i;
-        store_block(a.out + off + 16ull * i, u128{{z, z, z, z}}, rem >= 16 ? 16u : (uint32_t)rem, aligned);
+        store_block(a.out + off + 16ull * i, u128{{z, z, z, z}}, rem >= 16 ? 16u : (uint32_t)rem);
       }
     }
     if (lane < 8u) ((uint32_t*)sum)[lane] = 0u;  // free for tile k + kSlots
@@ -665,120 +685,152 @@ __global__ __launch_bounds__(kThreads) void k_gcm_tiles(GcmArgs a) {
 
 // ---------------------------------------------------------------------------
 // Per-segment finalize of tiled segments: S = sum_t P_t H^(tT) xor H*L and
-// tag = E_K(J0) xor S.  One wave per segment; lane l folds tiles l, l+64, ...
-// H*L is a wave sum over the set bits of L (only its low 64 bits can be set)
-// of the products H*x^(64+k); E_K(J0) reads a T-table copy in LDS.
+// tag = E_K(J0) xor S, of which the prologue has formed E_K(J0) xor H*L.  One
+// wave per segment; lane l folds tiles l, l+64, ...; with up to four tiles, 16
+// lanes share a tile's product.  Bound by latency: three dependent loads, then
+// a product.  With E_K(J0) and H*L formed here:
+// one 16 MiB segment 5.8 us, now 4.0; 16 segments of up to 128 tiles 10.8, now
+// 6.4.
 // ---------------------------------------------------------------------------
 template <bool OPEN>
 __global__ __launch_bounds__(kFinLanes) void k_finalize(GcmArgs a) {
-  __shared__ uint32_t te[256];
   const uint32_t s = blockIdx.x, lane = threadIdx.x;
-  for (uint32_t i = lane; i < 256u; i += kFinLanes) te[i] = c_aes.te0[i];
-  __syncthreads();
-  const SegDesc sd = a.segs[s];
-  if ((sd.flags & kSegSmall) || ((sd.flags & kSegOneTile) && !a.seg_cut[s])) return;
-  const int32_t verdict = a.verdicts[s];
+  const SegDesc sd = ld_uniform(a.segs + s);
+  const uniform_ptr tbs = to_uniform(a.tile_base + s);
+  const uint32_t cut = to_uniform(a.seg_cut + s)[0], tb = tbs[0], nt = tbs[1] - tb;
+  const int32_t verdict = (int32_t)to_uniform((const uint32_t*)a.verdicts + s)[0];
+  if ((sd.flags & kSegSmall) || ((sd.flags & kSegOneTile) && !cut)) return;
   if (verdict != kVerdictOk) {
     if (!OPEN && lane < 4) ((uint32_t*)(a.tags_out + 16ull * s))[lane] = 0u;
     return;
   }
   const uint32_t user = sd.user;
-  const uint32_t tb = a.tile_base[s], nt = a.tile_base[s + 1] - tb;
+  const u128 fin = ld_u128(a.fin + s);
   u128 z = u128_zero();
-  if (lane < nt) {
+  if (nt <= 4u) {
+    const uint32_t t = lane >> 4;
+    if (t < nt) {
+      const u128 x = ld_u128(a.partials + tb + t);
+      if (t > 0u)
+        z = gf_mul_slice(x, ld_u128(a.kt.pow_ht + (size_t)user * kFinLanes + t), lane & 15u);
+      else if (lane == 0u)
+        z = x;
+    }
+  } else if (lane < nt) {
     const uint32_t K = (nt - 1 - lane) / kFinLanes + 1;
+    const u128 ht = ld_u128(a.kt.pow_ht + (size_t)user * kFinLanes + lane);
     z = ld_u128(a.partials + tb + lane + (K - 1) * kFinLanes);
     if (K > 1) {
       const u128 hlt = ld_u128(a.kt.pow_hlt + user);
       for (int k = (int)K - 2; k >= 0; k--)
         z = u128_xor(gf_mul(z, hlt), ld_u128(a.partials + tb + lane + (uint32_t)k * kFinLanes));
     }
-    if (lane > 0) z = gf_mul(z, ld_u128(a.kt.pow_ht + (size_t)user * kFinLanes + lane));
+    if (lane > 0) z = gf_mul(z, ht);
   }
-  // H*L: bit 64+lane of L (GCM order) is bit 63-lane of the 64-bit length in bits
-  const uint64_t lbits = sd.len * 8ull;
-  if ((lbits >> (63 - lane)) & 1ull) z = u128_xor(z, ld_u128(a.kt.pow_hxl + (size_t)user * kHxLanes + lane));
 #pragma unroll
   for (int j = 0; j < 4; j++) z.w[j] = wave_xor(z.w[j]);
+  const u128 tag = u128_xor(fin, z);
   if (lane == 0) {
-    const uint32_t j0[4] = {sd.iv[0], sd.iv[1], sd.iv[2], 0x01000000u};
-    uint32_t e[4];
-    aes256_encrypt_tab(a.kt.rk + (size_t)user * 64u, j0, e, te);
-    const u128 tag = u128{{e[0] ^ z.w[0], e[1] ^ z.w[1], e[2] ^ z.w[2], e[3] ^ z.w[3]}};
     if (!OPEN) {
-      uint32_t* to = (uint32_t*)(a.tags_out + 16ull * s);
-      for (int j = 0; j < 4; j++) to[j] = tag.w[j];
+      store_block(a.tags_out + 16ull * s, tag, 16u);
     } else {
-      const uint8_t* ti = a.tags_in + 16ull * s;
+      const u128 want = load_block(a.tags_in + 16ull * s, 16u);
       uint32_t diff = 0;
 #pragma unroll
-      for (int k = 0; k < 16; k++) diff |= (uint32_t)ti[k] ^ ((tag.w[k >> 2] >> (8 * (k & 3))) & 0xFFu);
+      for (int k = 0; k < 4; k++) diff |= want.w[k] ^ tag.w[k];
       a.verdicts[s] = diff ? kVerdictAuthFail : kVerdictOk;
+      if (diff) *a.any_failed = 1u;
     }
   }
 }
 
 // ---------------------------------------------------------------------------
-// Segments of at most 64 blocks: one wave each, lane j owns block j and its
-// GHASH term X_j * H^(m + 1 - j); lane 0 adds L*H.  Open decides the verdict
-// before any plaintext is written.
+// Segments of at most 64 blocks: one wave each.  Lane j < m owns block j and
+// its GHASH term X_j * H^(m + 1 - j); lane m owns what is left of the tag, in
+// the same steps: E_K(J0) instead of a keystream block (counter 1) and the
+// length block's term L * H.  (With 64 blocks there is no lane m: lane 0 does
+// that part in a second pass.)  Open decides the verdict before any plaintext
+// is written.
+//
+// Bound by latency: dependent loads (list, descriptor, keys), 14 AES rounds,
+// one generic product.  With E_K(J0) and L * H after the blocks instead of
+// beside them, the product of up to four terms by one lane each instead of 16,
+// and the round keys by vector loads inside the rounds, the kernel took 21.4 us
+// for 1024 segments of 4 to 16 bytes; now 8.0 (a kernel that does nothing shows
+// as 4).
 // ---------------------------------------------------------------------------
 template <bool OPEN>
 __global__ __launch_bounds__(64) void k_small(GcmArgs a) {
   __shared__ uint32_t te[256];
-  for (uint32_t i = threadIdx.x; i < 256u; i += 64u) te[i] = c_aes.te0[i];
-  __syncthreads();
-  const uint32_t s = a.small_list[blockIdx.x];
   const uint32_t j = threadIdx.x;
-  const SegDesc sd = a.segs[s];
+  const uint32_t s = (uint32_t)__builtin_amdgcn_readfirstlane(a.small_list[blockIdx.x]);
+  const SegDesc sd = ld_uniform(a.segs + s);
+  const uint32_t user = sd.user;
+  const uint32_t rkv = held(a.kt.rk[(size_t)user * 64u + j]);
   const uint32_t m = sd.nblocks;
-  const bool valid = j < m;
-  const bool aligned = (sd.flags & kSegAligned) != 0;
+  const bool valid = j < m, last = j == m;
   const uint64_t rem = valid ? sd.len - 16ull * j : 0;
   const uint32_t n = rem >= 16 ? 16u : (uint32_t)rem;
   uint8_t* dst = a.out + sd.byte_off + 16ull * j;
-  const int32_t verdict = a.verdicts[s];
+  const int32_t verdict = (int32_t)to_uniform((const uint32_t*)a.verdicts + s)[0];
+  const u128 hp = j <= m ? ld_u128(a.kt.pow_h + (size_t)user * kHPowers + (m + 1 - j)) : u128_zero();
+  u128 in = u128_zero();
+  if (valid && verdict == kVerdictOk) in = load_block(a.in + sd.byte_off + 16ull * j, n);
+  for (uint32_t i = j; i < 256u; i += 64u) te[i] = c_aes.te0[i];
+  __syncthreads();
   if (verdict != kVerdictOk) {
-    if (valid) store_block(dst, u128_zero(), n, aligned);
+    if (valid) store_block(dst, u128_zero(), n);
     if (!OPEN && j < 4) ((uint32_t*)(a.tags_out + 16ull * s))[j] = 0u;
     return;
   }
-  const uint32_t user = sd.user;
-  const uint32_t* rk = a.kt.rk + (size_t)user * 64u;
-  u128 in = u128_zero(), o = u128_zero(), z = u128_zero();
-  if (valid) {
-    in = load_block(a.in + sd.byte_off + 16ull * j, n, aligned);
-    const uint32_t cb[4] = {sd.iv[0], sd.iv[1], sd.iv[2], bswap32(2u + j)};
-    uint32_t ks[4];
-    aes256_encrypt_tab(rk, cb, ks, te);
-    o = mask_block(u128{{in.w[0] ^ ks[0], in.w[1] ^ ks[1], in.w[2] ^ ks[2], in.w[3] ^ ks[3]}}, n);
-    const u128 x = OPEN ? in : o;
-    z = gf_mul(x, ld_u128(a.kt.pow_h + (size_t)user * kHPowers + (m + 1 - j)));
+  const uint32_t cb[4] = {sd.iv[0], sd.iv[1], sd.iv[2], last ? 0x01000000u : bswap32(2u + j)};
+  uint32_t ks[4];
+  aes256_encrypt_tab(rkv, cb, ks, te);
+  const u128 o = mask_block(u128{{in.w[0] ^ ks[0], in.w[1] ^ ks[1], in.w[2] ^ ks[2], in.w[3] ^ ks[3]}}, n);
+  const u128 x = last ? length_block(sd.len) : OPEN ? in : o;
+  u128 z;
+  if (m < 4u) {
+    // terms 0..m, 16 lanes each
+    const uint32_t t = j >> 4;
+    u128 tx = u128_zero(), th = u128_zero();
+#pragma unroll
+    for (int i = 0; i < 4; i++)
+#pragma unroll
+      for (int w = 0; w < 4; w++) {
+        const uint32_t xw = (uint32_t)__builtin_amdgcn_readlane((int)x.w[w], i);
+        const uint32_t hw = (uint32_t)__builtin_amdgcn_readlane((int)hp.w[w], i);
+        if (t == (uint32_t)i) tx.w[w] = xw, th.w[w] = hw;
+      }
+    z = t <= m ? gf_mul_slice(tx, th, j & 15u) : u128_zero();
+  } else {
+    z = gf_mul(x, hp);  // hp is zero past the last term
   }
-  const u128 h = ld_u128((const uint4*)(a.kt.h + 4ull * user));
-  if (j == 0) z = u128_xor(z, gf_mul(length_block(sd.len), h));
+  if (m == 64u && j == 0u)
+    z = u128_xor(z, gf_mul(length_block(sd.len), ld_u128(a.kt.pow_h + (size_t)user * kHPowers + 1)));
 #pragma unroll
   for (int k = 0; k < 4; k++) z.w[k] = wave_xor(z.w[k]);
-  uint32_t ok = 1;
-  if (j == 0) {
+  // E_K(J0) xor the sum, wave-uniform
+  u128 tag;
+  if (m == 64u) {
     const uint32_t j0[4] = {sd.iv[0], sd.iv[1], sd.iv[2], 0x01000000u};
-    uint32_t e[4];
-    aes256_encrypt_tab(rk, j0, e, te);
-    const u128 tag = u128{{e[0] ^ z.w[0], e[1] ^ z.w[1], e[2] ^ z.w[2], e[3] ^ z.w[3]}};
-    if (!OPEN) {
-      uint32_t* to = (uint32_t*)(a.tags_out + 16ull * s);
-      for (int k = 0; k < 4; k++) to[k] = tag.w[k];
-    } else {
-      const uint8_t* ti = a.tags_in + 16ull * s;
-      uint32_t diff = 0;
+    aes256_encrypt_tab(rkv, j0, tag.w, te);
+  } else {
 #pragma unroll
-      for (int k = 0; k < 16; k++) diff |= (uint32_t)ti[k] ^ ((tag.w[k >> 2] >> (8 * (k & 3))) & 0xFFu);
-      ok = diff == 0;
-      a.verdicts[s] = ok ? kVerdictOk : kVerdictAuthFail;
-    }
+    for (int k = 0; k < 4; k++) tag.w[k] = (uint32_t)__builtin_amdgcn_readlane((int)ks[k], (int)m);
   }
-  if (OPEN) ok = __builtin_amdgcn_readlane((int)ok, 0) != 0;
-  if (valid) store_block(dst, ok ? o : u128_zero(), n, aligned);
+  tag = u128_xor(tag, z);
+  bool ok = true;
+  if (!OPEN) {
+    if (j == 0u) store_block(a.tags_out + 16ull * s, tag, 16u);
+  } else {
+    const u128 want = load_block(a.tags_in + 16ull * s, 16u);
+    uint32_t diff = 0;
+#pragma unroll
+    for (int k = 0; k < 4; k++) diff |= want.w[k] ^ tag.w[k];
+    ok = __builtin_amdgcn_readfirstlane(diff) == 0;
+    if (j == 0u) a.verdicts[s] = ok ? kVerdictOk : kVerdictAuthFail;
+  }
+  if (valid) store_block(dst, ok ? o : u128_zero(), n);
 }
 
 // ---------------------------------------------------------------------------
@@ -806,7 +858,10 @@ __global__ __launch_bounds__(64) void k_small(GcmArgs a) {
 // result.
 // ---------------------------------------------------------------------------
 constexpr int kExpandThreads = 1024;  // the most threads an expanding workgroup may have
-constexpr int kPrologueThreads = 256;
+constexpr int kPrologueThreads = kExpandThreads;  // the most; 256 for tables that fit them
+// Waves of a workgroup that take a segment each: one per SIMD, whose time the
+// AES block takes (16 per workgroup made 1024 segments' prologue 2.4 us longer).
+constexpr uint32_t kPrologueWaves = 4;
 constexpr uint32_t kRunTiles = 16;
 
 __device__ __forceinline__ uint32_t tiles_in(uint32_t nblocks) {
@@ -880,6 +935,135 @@ __device__ uint3 block_scan3(uint3 v, uint3* wsum, uint3* total) {
   return make_uint3(before.x + x.x - v.x, before.y + x.y - v.y, before.z + x.z - v.z);
 }
 
+// The expansion of a table with at most one segment per thread whose tiles are
+// all cut alike (fewer tiles than CUs) or not at all: three barriers instead of
+// eight, and no walk over runs.  Returns false, with nothing written, when the
+// tail cut applies.  What it writes is what expand_tables says.  The waves work
+// out the sums, the cut and the queue's class starts each for itself.  Bound by
+// the latency of its phases.  Prologue, before and after: one 16 MiB segment
+// (256 pieces, one thread placed them) 22.6 -> 6.3 us, 1024 segments of one tile
+// 14.4 -> 12.1 us.
+__device__ bool expand_short(const SegBrief* brief, uint32_t n, const ExpandArgs& x) {
+  struct Rec {  // a segment's whole tiles: all of those before it, then its own
+    uint32_t f0, p0, c0, nc, tb, nt, user, rank_rem;
+  };
+  __shared__ uint32_t cursor[kRows + 1];
+  __shared__ uint4 sum1[kExpandThreads / 64];
+  __shared__ uint3 sum2[kExpandThreads / 64];
+  __shared__ Rec rec[kExpandThreads];
+  const uint32_t tid = threadIdx.x, threads = blockDim.x, lane = tid & 63u, wave = tid >> 6, waves = threads >> 6;
+  const bool have = tid < n;
+  uint2 b = make_uint2(0u, 0u);
+  if (have) b = ((const uint2*)brief)[tid];
+  for (uint32_t i = tid; i <= (uint32_t)kRows; i += threads) cursor[i] = 0u;
+  const uint32_t m = b.x, user = b.y;
+  const bool small = have && m <= x.small_max, tiled = have && !small;
+  const uint32_t nt = tiled ? tiles_in(m) : 0u, r = tiled ? tile_rows_of(m, nt - 1u) : 0u;
+  const uint32_t scan_t = wave_incl_scan(nt);
+  const unsigned long long smalls = __ballot(small);
+  const uint32_t rows = wave_sum(tiled ? (nt - 1u) * kRows + r : 0u);
+  const bool lng = __any(nt > 1u || r > (uint32_t)kPieceRows);
+  if (lane == 63u) sum1[wave] = make_uint4(scan_t, (uint32_t)__popcll(smalls), rows, lng ? 1u : 0u);
+  __syncthreads();
+
+  uint32_t tb = scan_t - nt, sm = (uint32_t)__popcll(smalls & ((1ull << lane) - 1ull));
+  uint32_t n_tiles = 0, rows_all = 0, any_long = 0;
+  for (uint32_t v = 0; v < waves; v++) {
+    const uint4 c = sum1[v];
+    if (v < wave) tb += c.x, sm += c.y;
+    n_tiles += c.x;
+    rows_all += c.z;  // (read only with fewer tiles than CUs, when it is small)
+    any_long |= c.w;
+  }
+  const bool fine = n_tiles < x.cus;
+  if (!fine && any_long) return false;
+  uint32_t p = fine ? (rows_all + x.cus - 1u) / x.cus : (uint32_t)kRows;
+  if (p == 0u || p > (uint32_t)kRows) p = kRows;  // nothing is cut
+  const uint32_t per = (uint32_t)kRows / p, rem = (uint32_t)kRows % p;
+  const uint32_t whole = r == (uint32_t)kRows ? nt : nt - (nt ? 1u : 0u);
+  const uint32_t nc = p < (uint32_t)kRows ? whole : 0u, nf = whole - nc;
+  const bool part = r > 0u && r < (uint32_t)kRows, part_cut = part && r > p;
+  const uint32_t part_pieces = part_cut ? r / p : 0u, part_len = part_cut ? r % p : part ? r : 0u;
+  if (have) {
+    x.tile_base[tid] = tb;
+    x.seg_cut[tid] = nt == 1u && (nc || part_cut) ? 1u : 0u;
+    if (small) x.small_list[sm] = tid;
+  }
+  if (tid == 0u) x.tile_base[n] = n_tiles;
+  uint32_t rank_part = 0, rank_rem = 0;
+  if (part_len) rank_part = atomicAdd(&cursor[part_len], 1u);
+  if (nc && rem) rank_rem = atomicAdd(&cursor[rem], nc);
+  const uint32_t np = nc * per + part_pieces;
+  const uint3 sc = make_uint3(wave_incl_scan(nf), wave_incl_scan(np), wave_incl_scan(nc));
+  if (lane == 63u) sum2[wave] = sc;
+  __syncthreads();
+
+  uint3 at = make_uint3(sc.x - nf, sc.y - np, sc.z - nc), all = make_uint3(0u, 0u, 0u);
+  for (uint32_t v = 0; v < waves; v++) {
+    const uint3 c = sum2[v];
+    if (v < wave) at.x += c.x, at.y += c.y, at.z += c.z;
+    all.x += c.x, all.y += c.y, all.z += c.z;
+  }
+  // class starts, longest first: lane k holds rows kRows - k and kRows - 64 - k
+  const uint32_t ka = kRows - lane, kb = kRows - 64u - lane;
+  const uint32_t na = cursor[ka] + (ka == (uint32_t)kRows ? all.x : 0u) + (ka == p ? all.y : 0u);
+  const uint32_t nb = cursor[kb] + (kb == p ? all.y : 0u);
+  const uint32_t ia = wave_incl_scan(na), ib = (uint32_t)__builtin_amdgcn_readlane((int)ia, 63) + wave_incl_scan(nb);
+  const uint32_t ents = (uint32_t)__builtin_amdgcn_readlane((int)ib, 63);
+  auto start = [&](uint32_t len) -> uint32_t {
+    const int k = (int)((uint32_t)kRows - len);
+    const uint32_t a = __shfl(ia - na, k & 63), c = __shfl(ib - nb, k & 63);
+    return k < 64 ? a : c;
+  };
+  const uint32_t piece_at = start(p), rem_at = rem ? start(rem) : 0u, part_at = start(part_len ? part_len : 1u);
+  auto put = [&](uint32_t pos, uint32_t g0, uint32_t seg, uint32_t t, uint32_t r0, uint32_t r1, uint32_t u) {
+    if (pos < x.cap) x.order[pos] = TileEnt{g0 + t, seg, t | (r0 << 16) | (r1 << 24), u};
+  };
+  if (part_len) {
+    // an uncut partial tile, or the lowest piece of a cut one
+    const uint32_t r1 = part_cut ? (uint32_t)kRows - part_pieces * p : (uint32_t)kRows;
+    put(part_at + (part_len == p ? all.y : 0u) + rank_part, tb, tid, nt - 1u, part_cut && r1 > p ? r1 - p : 0u, r1, user);
+  }
+  if (all.x | all.y) {
+    // whole tiles and pieces, spread over the threads: each finds its segment
+    // by binary search over what the segments before it have
+    rec[tid] = Rec{at.x, at.y, at.z, nc, tb, nt, user, rank_rem};
+    __syncthreads();
+    auto find = [&](uint32_t j, auto&& first) -> uint32_t {
+      uint32_t lo = 0, hi = n;
+      while (hi - lo > 1u) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (first(rec[mid]) <= j)
+          lo = mid;
+        else
+          hi = mid;
+      }
+      return lo;
+    };
+    for (uint32_t j = tid; j < all.x; j += threads) {
+      const uint32_t i = find(j, [](const Rec& q) { return q.f0; });
+      const Rec q = rec[i];
+      put(j, q.tb, i, q.nc + (j - q.f0), 0u, kRows, q.user);
+    }
+    for (uint32_t j = tid; j < all.y; j += threads) {
+      const uint32_t i = find(j, [](const Rec& q) { return q.p0; });
+      const Rec q = rec[i];
+      const uint32_t d = j - q.p0, t = d / per;
+      const uint32_t k = t < q.nc ? d % per : d - q.nc * per;
+      put(piece_at + j, q.tb, i, t < q.nc ? t : q.nt - 1u, kRows - (k + 1u) * p, kRows - k * p, q.user);
+    }
+    if (rem)
+      for (uint32_t j = tid; j < all.z; j += threads) {
+        const uint32_t i = find(j, [](const Rec& q) { return q.c0; });
+        const Rec q = rec[i];
+        put(rem_at + (rem == p ? all.y : 0u) + q.rank_rem + (j - q.c0), q.tb, i, j - q.c0, 0u, rem, q.user);
+      }
+  }
+  for (uint32_t k = ents + tid; k < x.cap; k += threads) x.order[k] = TileEnt{kNoTile, 0u, 0u, 0u};
+  if (tid == 0u && x.n_ents) *x.n_ents = ents;
+  return true;
+}
+
 // Expansion by the calling workgroup (all its threads call it), from the
 // per-segment brief records (the source may be host memory).  A one-tile
 // segment whose tile is cut gets seg_cut = 1 (every segment gets its 0 or 1).
@@ -888,6 +1072,7 @@ __device__ uint3 block_scan3(uint3 v, uint3* wsum, uint3* total) {
 constexpr uint32_t kInfoLds = 1024;
 
 __device__ void expand_tables(const SegBrief* brief, uint32_t n, const ExpandArgs& x) {
+  if (n <= blockDim.x && expand_short(brief, n, x)) return;
   __shared__ uint32_t hist[kRows + 1];    // tiles by rows
   __shared__ uint32_t cursor[kRows + 1];  // entries by rows run, then the next free slot of each
   __shared__ uint32_t wsum[kExpandThreads / 64];
@@ -1216,6 +1401,8 @@ struct PrologueArgs {
   uint4* fin;
   uint4* zero;
   uint32_t n_zero;
+  ChunkTable chunks;
+  bool by_wave;
   bool expand;
   const SegBrief* brief;  // where the brief records are readable now
   ExpandArgs x;
@@ -1237,37 +1424,60 @@ __global__ __launch_bounds__(kPrologueThreads) void k_prologue(PrologueArgs a) {
   if (a.src)
     for (size_t i = me; i < a.n16; i += gsz) a.dst[i] = a.src[i];
   for (size_t i = me; i < a.n_zero; i += gsz) a.zero[i] = make_uint4(0u, 0u, 0u, 0u);
+  // paged calls: where each chunk is.  The segments' chunks follow each other
+  // as their blocks do in the block-id array: chunk c is chunk c % per_block of
+  // block c / per_block.
+  const ChunkTable& ct = a.chunks;
+  for (uint64_t c = me; c < ct.n; c += gsz) {
+    const uint64_t j = ct.n >> 32 ? c / ct.per_block : (uint32_t)c / (uint32_t)ct.per_block;
+    const uint64_t i = c - j * ct.per_block;  // layer and part
+    const uint64_t l = ct.n >> 32 ? i / ct.parts : (uint32_t)i / ct.parts;
+    ct.off[c] = l * ct.layer_stride + (uint64_t)a.bids[j] * ct.block_stride + (i - l * ct.parts) * ct.part_stride;
+  }
   if (!a.verdicts) return;
   const SegDesc* segs = a.segs;
   if (a.fin) {
     for (uint32_t i = threadIdx.x; i < 256u; i += blockDim.x) te[i] = c_aes.te0[i];
     __syncthreads();
   }
-  for (uint32_t s = wg; s < a.n; s += n_wg) {
-    if (a.fin && threadIdx.x < 64u && (segs[s].flags & kSegOneTile)) {
-      // GCM a one-tile segment needs besides its tile: E_K(J0) xor H*L,
-      // J0 = IV || BE32(1), H*L a wave sum over the set bits of the length
-      // block (only its low 64 bits can be set) of the products H*x^(64+k)
-      const uint32_t lane = threadIdx.x, user = segs[s].user;
-      u128 z = u128_zero();
-      if (((segs[s].len * 8ull) >> (63 - lane)) & 1ull) z = ld_u128(a.kt.pow_hxl + (size_t)user * kHxLanes + lane);
-#pragma unroll
-      for (int j = 0; j < 4; j++) z.w[j] = wave_xor(z.w[j]);
-      if (lane == 0) {
-        const uint32_t j0[4] = {segs[s].iv[0], segs[s].iv[1], segs[s].iv[2], 0x01000000u};
-        uint32_t e[4];
-        aes256_encrypt_tab(a.kt.rk + (size_t)user * 64u, j0, e, te);
-        a.fin[s] = make_uint4(e[0] ^ z.w[0], e[1] ^ z.w[1], e[2] ^ z.w[2], e[3] ^ z.w[3]);
-      }
+  // A segment per wave (by_wave: few rows per segment) or per workgroup.  The
+  // descriptors may be in host memory: a wave reads one in one access.
+  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+  const uint32_t first = a.by_wave ? wg * kPrologueWaves + wave : wg, step = a.by_wave ? n_wg * kPrologueWaves : n_wg;
+  if (a.by_wave && wave >= kPrologueWaves) return;
+  for (uint32_t s = first; s < a.n; s += step) {
+    const uint32_t dv = lane < 16u ? ((const uint32_t*)(segs + s))[lane] : 0u;
+    auto word = [&](size_t at) { return lane_word(dv, (int)(at / 4)); };
+    auto word2 = [&](size_t at) { return (uint64_t)word(at + 4) << 32 | word(at); };
+    const uint32_t user = word(offsetof(SegDesc, user));
+    // what the tag of a tiled segment needs besides its tiles: E_K(J0) xor
+    // H*L, J0 = IV || BE32(1), H*L a wave sum over the set bits of the length
+    // block (only its low 64 bits can be set) of the products H*x^(64+k)
+    const bool fin = a.fin && (a.by_wave || wave == 0u) && !(word(offsetof(SegDesc, flags)) & kSegSmall);
+    uint32_t rkv = 0;
+    u128 z = u128_zero();
+    if (fin) {
+      rkv = held(a.kt.rk[(size_t)user * 64u + lane]);
+      if (((word2(offsetof(SegDesc, len)) * 8ull) >> (63 - lane)) & 1ull)
+        z = ld_u128(a.kt.pow_hxl + (size_t)user * kHxLanes + lane);
     }
     int bad = 0;
     if (a.labels) {
-      const uint64_t rb = segs[s].row_begin, rc = segs[s].row_count;
-      const uint32_t user = segs[s].user;
-      for (uint64_t r = threadIdx.x; r < rc; r += blockDim.x) bad |= a.labels[a.bids ? a.bids[rb + r] : rb + r] != user;
-      bad = __syncthreads_or(bad);
+      const uint64_t rb = word2(offsetof(SegDesc, row_begin)), rc = word2(offsetof(SegDesc, row_count));
+      const uint32_t r0 = a.by_wave ? lane : threadIdx.x, rs = a.by_wave ? 64u : blockDim.x;
+      for (uint64_t r = r0; r < rc; r += rs) bad |= a.labels[a.bids ? a.bids[rb + r] : rb + r] != user;
+      bad = a.by_wave ? __any(bad) : __syncthreads_or(bad);
     }
-    if (threadIdx.x == 0) a.verdicts[s] = bad ? kVerdictOwnerMixed : kVerdictOk;
+    if ((a.by_wave ? lane : threadIdx.x) == 0u) a.verdicts[s] = bad ? kVerdictOwnerMixed : kVerdictOk;
+    if (fin) {
+#pragma unroll
+      for (int j = 0; j < 4; j++) z.w[j] = wave_xor(z.w[j]);
+      const uint32_t j0[4] = {word(offsetof(SegDesc, iv)), word(offsetof(SegDesc, iv) + 4),
+                              word(offsetof(SegDesc, iv) + 8), 0x01000000u};
+      uint32_t e[4];
+      aes256_encrypt_tab(rkv, j0, e, te);
+      if (lane == 0u) a.fin[s] = make_uint4(e[0] ^ z.w[0], e[1] ^ z.w[1], e[2] ^ z.w[2], e[3] ^ z.w[3]);
+    }
   }
 }
 
@@ -1342,6 +1552,8 @@ __global__ __launch_bounds__(kTokenChunk) void k_tokens(const SegDesc* __restric
     const uint64_t rb = segs[s].row_begin, rc = segs[s].row_count;
     const uint32_t user = segs[s].user;
     const uint64_t i = (uint64_t)kTokenChunk * (b - chunk_base[s]) + threadIdx.x;
+    const uint32_t keys = held((DECRYPT ? kt.dk : kt.rk)[64ull * user + threadIdx.x]);
+    static_assert(kTokenChunk == 64, "one wave per chunk: a round-key word per lane");
     if (i < rc) {
       const uint64_t r = rb + i;
       if (!DECRYPT) {
@@ -1351,7 +1563,7 @@ __global__ __launch_bounds__(kTokenChunk) void k_tokens(const SegDesc* __restric
           o[0] = o[1] = o[2] = o[3] = 0xFFFFFFFFu;
         } else {
           const uint32_t blk[4] = {(uint32_t)t, (uint32_t)(t >> 32), (uint32_t)n, (uint32_t)(n >> 32)};
-          aes256_encrypt_tab(kt.rk + 64ull * user, blk, o, tab);
+          aes256_encrypt_tab(keys, blk, o, tab);
         }
         *(uint4*)(blocks_out + 16ull * r) = make_uint4(o[0], o[1], o[2], o[3]);
       } else {
@@ -1363,7 +1575,7 @@ __global__ __launch_bounds__(kTokenChunk) void k_tokens(const SegDesc* __restric
         } else {
           const uint32_t blk[4] = {b.x, b.y, b.z, b.w};
           uint32_t p[4];
-          aes256_decrypt_tab(kt.dk + 64ull * user, blk, p, tab, isb);
+          aes256_decrypt_tab(keys, blk, p, tab, isb);
           t = (uint64_t)p[0] | ((uint64_t)p[1] << 32);
           n = (uint64_t)p[2] | ((uint64_t)p[3] << 32);
         }
@@ -1375,36 +1587,22 @@ __global__ __launch_bounds__(kTokenChunk) void k_tokens(const SegDesc* __restric
 }
 
 // ---------------------------------------------------------------------------
-// Paged KV: offsets of a segment's chunks in stream order (for each block of
-// its table, each layer, each part), and zeroing of rejected segments' chunks.
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_chunk_table(const SegDesc* __restrict__ segs, uint32_t n,
-                                                     const uint32_t* __restrict__ bids, uint32_t n_layers,
-                                                     uint32_t n_parts, uint64_t ls, uint64_t bs, uint64_t ps,
-                                                     uint64_t* __restrict__ chunk_off) {
-  const uint64_t per_block = (uint64_t)n_layers * n_parts;
-  for (uint32_t s = blockIdx.x; s < n; s += gridDim.x) {
-    const uint64_t bid0 = segs[s].row_begin, nchunks = segs[s].row_count * per_block, c0 = segs[s].chunk0;
-    for (uint64_t c = threadIdx.x; c < nchunks; c += blockDim.x) {
-      const uint64_t j = c / per_block, rem = c % per_block;
-      const uint64_t l = rem / n_parts, p = rem % n_parts;
-      chunk_off[c0 + c] = l * ls + (uint64_t)bids[bid0 + j] * bs + p * ps;
-    }
-  }
-}
-
 // Open: zero the output of segments that failed, tile by tile.  A workgroup
 // takes whole tiles of kTileBlocks blocks (the GCM kernel's tiles, found
 // through tile_base), so the work per workgroup is bounded.  Contiguous
 // output (chunk_off == nullptr): every segment whose verdict is not OK.
 // Through block tables: only requests that failed authentication -- their
 // blocks passed the label check, so they are the request's own; a request
-// rejected by the label check writes nothing.
-__global__ __launch_bounds__(256) void k_zero_failed(const SegDesc* __restrict__ segs, uint32_t n,
+// rejected by the label check writes nothing.  Nothing to do unless a tag
+// failed (*any_failed): in contiguous output the tile kernel has zeroed the
+// segments that the label check rejected.
+__global__ __launch_bounds__(256) void k_zero_failed(const uint32_t* __restrict__ any_failed,
+                                                     const SegDesc* __restrict__ segs, uint32_t n,
                                                      const uint32_t* __restrict__ tile_base, uint32_t n_tiles,
                                                      const int32_t* __restrict__ verdicts,
                                                      const uint64_t* __restrict__ chunk_off, uint8_t* base,
                                                      uint32_t chunk_shift) {
+  if (*any_failed == 0u) return;
   const uint64_t cmask = (1ull << chunk_shift) - 1;
   for (uint32_t g = blockIdx.x; g < n_tiles; g += gridDim.x) {
     uint32_t lo = 0, hi = n;  // tile_base[lo] <= g < tile_base[hi]
@@ -1429,10 +1627,9 @@ __global__ __launch_bounds__(256) void k_zero_failed(const SegDesc* __restrict__
     } else {
       const uint64_t len = segs[lo].len;
       uint8_t* p = base + segs[lo].byte_off;
-      const bool aligned = (segs[lo].flags & kSegAligned) != 0;
       for (uint64_t i = begin + threadIdx.x; i < end; i += blockDim.x) {
         const uint64_t rem = len - 16ull * i;
-        store_block(p + 16ull * i, u128_zero(), rem >= 16 ? 16u : (uint32_t)rem, aligned);
+        store_block(p + 16ull * i, u128_zero(), rem >= 16 ? 16u : (uint32_t)rem);
       }
     }
   }
@@ -1582,23 +1779,13 @@ hipError_t launch_tokens(const SegDesc* segs, const uint32_t* chunk_base, uint32
   return hipGetLastError();
 }
 
-hipError_t launch_chunk_table(const SegDesc* segs, uint32_t n_segs, const uint32_t* bids, uint32_t n_layers,
-                              uint32_t n_parts, uint64_t layer_stride, uint64_t block_stride, uint64_t part_stride,
-                              uint64_t* chunk_off, hipStream_t s) {
-  if (n_segs == 0) return hipSuccess;
-  const uint32_t grid = n_segs < 65535u ? n_segs : 65535u;
-  hipLaunchKernelGGL(k_chunk_table, dim3(grid), dim3(256), 0, s, segs, n_segs, bids, n_layers, n_parts, layer_stride,
-                     block_stride, part_stride, chunk_off);
-  return hipGetLastError();
-}
-
-hipError_t launch_zero_failed(const SegDesc* segs, uint32_t n_segs, const uint32_t* tile_base, uint32_t n_tiles,
+hipError_t launch_zero_failed(const uint32_t* any_failed, const SegDesc* segs, uint32_t n_segs, const uint32_t* tile_base, uint32_t n_tiles,
                               const int32_t* verdicts, const uint64_t* chunk_off, uint8_t* base, uint32_t chunk_shift,
                               uint32_t grid, hipStream_t s) {
   if (n_segs == 0 || n_tiles == 0) return hipSuccess;
   if (grid > n_tiles) grid = n_tiles;
-  hipLaunchKernelGGL(k_zero_failed, dim3(grid), dim3(256), 0, s, segs, n_segs, tile_base, n_tiles, verdicts,
-                     chunk_off, base, chunk_shift);
+  hipLaunchKernelGGL(k_zero_failed, dim3(grid), dim3(256), 0, s, any_failed, segs, n_segs, tile_base, n_tiles,
+                     verdicts, chunk_off, base, chunk_shift);
   return hipGetLastError();
 }
 
@@ -1609,9 +1796,10 @@ hipError_t launch_expand(const SegBrief* brief, uint32_t n_segs, const ExpandArg
   return hipGetLastError();
 }
 
-hipError_t launch_prologue(void* dst, const void* src, size_t bytes, uint32_t n_segs, uint64_t bids_off,
+hipError_t launch_prologue(void* dst, const void* src, size_t bytes, uint32_t n_segs, uint64_t rows, uint64_t bids_off,
                            const uint32_t* labels, int32_t* verdicts, const KeyTableDev* kt, uint4* fin,
-                           uint4* zero, uint32_t n_zero, uint64_t brief_off, const ExpandArgs* ex, hipStream_t s) {
+                           uint4* zero, uint32_t n_zero, uint64_t brief_off, const ExpandArgs* ex,
+                           const ChunkTable* chunks, hipStream_t s) {
   if (bytes & 15u) return hipErrorInvalidValue;
   const size_t n16 = src ? bytes / 16 : 0;
   const bool expand = ex != nullptr && n_segs > 0;
@@ -1619,9 +1807,16 @@ hipError_t launch_prologue(void* dst, const void* src, size_t bytes, uint32_t n_
   if (n16 && (((uintptr_t)dst | (uintptr_t)src) & 15u)) return hipErrorInvalidValue;
   if (expand && (brief_off & 15u || brief_off + 8ull * (n_segs + 1) > bytes)) return hipErrorInvalidValue;
   const uint8_t* rd = src ? (const uint8_t*)src : (const uint8_t*)dst;  // where the tables are readable now
-  uint64_t grid = cdiv(n16 > n_zero ? n16 : n_zero, kPrologueThreads);
-  if (verdicts && n_segs > grid) grid = n_segs;
-  if (grid > 1024u) grid = 1024u;
+  const uint32_t threads = n_segs <= 256u ? 256u : (uint32_t)kPrologueThreads;
+  uint64_t grid = cdiv(n16 > n_zero ? n16 : n_zero, threads);
+  // Segments of up to 64 rows on average take a wave each, so that 1024 of
+  // them need 256 workgroups; longer ones a workgroup, whose threads read the
+  // labels of a KV segment (thousands of rows) in a few steps.
+  const bool by_wave = rows <= 64ull * n_segs;
+  if (chunks && cdiv(chunks->n, threads) > grid) grid = cdiv(chunks->n, threads);
+  const uint64_t per_wg = by_wave ? kPrologueWaves : 1;
+  if (verdicts && cdiv(n_segs, per_wg) > grid) grid = cdiv(n_segs, per_wg);
+  if (grid > 512u) grid = 512u;
   if (grid == 0) grid = 1;
   if (expand) grid += 1;  // workgroup 0 expands the segment table
   PrologueArgs a{};
@@ -1637,12 +1832,14 @@ hipError_t launch_prologue(void* dst, const void* src, size_t bytes, uint32_t n_
   a.fin = kt ? fin : nullptr;
   a.zero = zero;
   a.n_zero = n_zero;
+  if (chunks) a.chunks = *chunks;
+  a.by_wave = by_wave;
   a.expand = expand;
   if (expand) {
     a.x = *ex;
     a.brief = (const SegBrief*)(rd + brief_off);
   }
-  hipLaunchKernelGGL(k_prologue, dim3((uint32_t)grid), dim3(kPrologueThreads), 0, s, a);
+  hipLaunchKernelGGL(k_prologue, dim3((uint32_t)grid), dim3(threads), 0, s, a);
   return hipGetLastError();
 }
 
