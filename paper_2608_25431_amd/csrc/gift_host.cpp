@@ -231,6 +231,13 @@ class Staging {
     return e;
   }
 
+  // Whether upload() hands consume() a device address for tables of up to
+  // kMaxStaged bytes (a multiple of 16).
+  bool mapped() {
+    std::lock_guard<std::mutex> g(mu_);
+    return ring() == hipSuccess && dbase_ != nullptr;
+  }
+
   // Copies bytes into the ring, then consume(src) enqueues on s the kernel
   // that reads them and the rest of the call's work: src is the copy's
   // device address, or nullptr when the bytes were DMA-copied to dst instead
@@ -1316,61 +1323,67 @@ static gift_status run_tokens(bool decrypt, const gift_segment_table* st, uint64
   int dev;
   if ((sv = current_device(&dev)) != GIFT_OK) return sv;
   if (dev != kt->device) return fail(GIFT_E_INVALID, "key table belongs to device %d, current is %d", kt->device, dev);
-  Plan P;
-  build_plan(st->segs, n, n_tokens, 1, nullptr, nullptr, nullptr, P);
-  // staged: the descriptors, then the first 64-token chunk of each segment
-  // (an exclusive scan; the token kernel's work items are these chunks)
-  const size_t o_cb = sizeof(SegDesc) * n;
-  const size_t staged = o_cb + ((4ull * (n + 1) + 15) & ~(size_t)15);
-  std::vector<uint8_t> host(n > 0 ? staged : 0);
-  uint64_t n_chunks = 0;
-  if (n > 0) {
-    memcpy(host.data(), P.descs.data(), o_cb);
-    uint32_t* cb = (uint32_t*)(host.data() + o_cb);
-    for (uint32_t i = 0; i < n; i++) {
-      cb[i] = (uint32_t)n_chunks;
-      n_chunks += (st->segs[i].row_count + kTokenChunk - 1) / kTokenChunk;
-      if (n_chunks > UINT32_MAX) return fail(GIFT_E_TOO_LARGE, "more than 2^32 - 1 chunks of %u tokens", kTokenChunk);
-    }
-    cb[n] = (uint32_t)n_chunks;
+  uint64_t n_chunks = 0, covered = 0;
+  for (uint32_t i = 0; i < n; i++) {
+    covered += st->segs[i].row_count;
+    n_chunks += (st->segs[i].row_count + kTokenChunk - 1) / kTokenChunk;
+    if (n_chunks > UINT32_MAX) return fail(GIFT_E_TOO_LARGE, "more than 2^32 - 1 chunks of %u tokens", kTokenChunk);
   }
-  SegDesc* d = nullptr;
+  // Staged: a record per run of tokens.  A run is one chunk, so that a long
+  // segment spreads over the chip; from 16384 chunks on it grows, so that the
+  // table stays small beside the tokens (each 32 B).
+  const uint64_t run_max = kTokenChunk * (n_chunks / 16384 + 1);
+  std::vector<TokenRun> runs;
+  runs.reserve(n + n_chunks * kTokenChunk / run_max + 1);
+  for (uint32_t i = 0; i < n; i++) {
+    const gift_segment& g = st->segs[i];
+    for (uint64_t r = 0; r < g.row_count; r += run_max)
+      runs.push_back(TokenRun{g.row_begin + r, g.user, (uint32_t)std::min(run_max, g.row_count - r)});
+  }
+  const size_t staged = sizeof(TokenRun) * runs.size();
+  // The kernel reads up to kDirectRuns records from the staging ring itself, a
+  // host read per workgroup that all of them make at once (about 2 us); more
+  // are copied to device scratch in whole cache lines first.
+  constexpr size_t kDirectRuns = 4096;
+  Staging* sg = staging_for(dev);
+  if (!sg) return fail(GIFT_E_INVALID, "device index %d unsupported", dev);
+  const bool direct = runs.size() <= kDirectRuns && sg->mapped();
+  TokenRun* d = nullptr;
   hipError_t e = hipSuccess;
   ScratchLease lease;
-  if (n > 0) {
+  if (n > 0 && !direct) {
     e = lease.acquire(dev, stream, staged);
     if (e != hipSuccess) return hip_fail(e, "device scratch");
-    d = (SegDesc*)lease.ptr;
+    d = (TokenRun*)lease.ptr;
   }
-  // uncovered tokens (rows no segment covers) get zero output: only when the
-  // plan has such gaps is the output cleared first, the token kernel then
-  // overwrites every covered entry
-  const bool gaps = !P.zr.empty();
+  // uncovered tokens (rows no segment covers; segments do not overlap) get
+  // zero output: only when there are any is the output cleared first, the
+  // token kernel then overwrites every covered entry
+  const bool gaps = covered < n_tokens;
   EventMark call_ev;  // the event recorded behind the call's last kernel
-  auto rest = [&]() -> hipError_t {
+  auto rest = [&](const TokenRun* table) -> hipError_t {
     hipError_t r = hipSuccess;
     if (gaps)
       r = decrypt ? launch_wipe(tokens_out, 8ull * n_tokens, stream) : launch_wipe(blocks_out, 16ull * n_tokens, stream);
     if (r == hipSuccess && gaps && decrypt && nonces_out) r = launch_wipe(nonces_out, 8ull * n_tokens, stream);
     if (r == hipSuccess)
-      r = launch_tokens(d, (const uint32_t*)((const uint8_t*)d + o_cb), n, (uint32_t)n_chunks, decrypt, tokens,
-                        nonces, blocks_in, blocks_out, tokens_out, nonces_out, eos_token, kt->dev, stream);
+      r = launch_tokens(table, (uint32_t)runs.size(), decrypt, tokens, nonces, blocks_in, blocks_out, tokens_out,
+                        nonces_out, eos_token, kt->dev, stream);
     return r;
   };
   if (n > 0) {
     // the token kernels are enqueued while the staging slot is held (one
     // event behind the last of them frees the slot)
-    Staging* sg = staging_for(dev);
-    e = sg ? sg->upload(d, host.data(), staged, stream,
-                        [&](const void* src) {
-                          hipError_t r = launch_prologue(d, src, staged, n, 0, kNoBids, nullptr, nullptr, nullptr,
-                                                         nullptr, nullptr, 0u, 0u, nullptr, nullptr, stream);
-                          return r != hipSuccess ? r : rest();
-                        },
-                        false, &call_ev)
-           : hipErrorInvalidDevice;
+    e = sg->upload(d, runs.data(), staged, stream,
+                   [&](const void* src) {
+                     if (direct) return rest((const TokenRun*)src);
+                     hipError_t r = launch_prologue(d, src, staged, 0, 0, kNoBids, nullptr, nullptr, nullptr, nullptr,
+                                                    nullptr, 0u, 0u, nullptr, nullptr, stream);
+                     return r != hipSuccess ? r : rest(d);
+                   },
+                   false, &call_ev);
   } else {
-    e = rest();
+    e = rest(nullptr);
   }
   hipError_t e2 = lease.release(call_ev);
   if (e != hipSuccess) return hip_fail(e, "token kernels");

@@ -1511,51 +1511,44 @@ __global__ __launch_bounds__(256) void k_wipe(uint8_t* p, size_t bytes) {
 
 // ---------------------------------------------------------------------------
 // Per-token encryption (token || nonce as one block under the owner's key,
-// the end-of-sequence token as the all-0xFF block).  The work is cut into
-// chunks of 64 tokens of one segment: chunk_base[s] is the first chunk of
-// segment s (an exclusive scan of ceil(row_count / 64), chunk_base[n_segs] =
-// n_chunks), and a workgroup of 64 threads takes one chunk at a time,
-// finding its segment by binary search.  Outputs of uncovered tokens were
-// zeroed before this launch.
+// the end-of-sequence token as the all-0xFF block).  The work is cut into runs
+// of tokens of one segment, one per workgroup of 64 threads, whose records the
+// host writes (16 B: all that the kernel needs of a segment); they may be in
+// host memory.  Outputs of uncovered tokens were zeroed before this launch.
+//
+// Bound by latency: the record, then keys and tokens, then 14 AES rounds.  With
+// a prologue kernel that copied the descriptors to the device and a search for
+// each workgroup's segment there, a call on 1024 segments of 1-4 tokens took
+// 24.3 us, now 17.1, which is the host's share; 64 prompts of 128-2048 tokens
+// 16.1, now 14.5.
 // ---------------------------------------------------------------------------
 template <bool DECRYPT>
-__global__ __launch_bounds__(kTokenChunk) void k_tokens(const SegDesc* __restrict__ segs,
-                                                        const uint32_t* __restrict__ chunk_base, uint32_t n_segs,
-                                                        uint32_t n_chunks,
-                                               const uint64_t* __restrict__ tokens,
-                                               const uint64_t* __restrict__ nonces,
-                                               const uint8_t* __restrict__ blocks_in, uint8_t* __restrict__ blocks_out,
-                                               uint64_t* __restrict__ tokens_out, uint64_t* __restrict__ nonces_out,
-                                               uint64_t eos_token, KeyTableDev kt) {
+__global__ __launch_bounds__(kTokenChunk) void k_tokens(const TokenRun* __restrict__ runs, uint32_t n_runs,
+                                                        const uint64_t* __restrict__ tokens,
+                                                        const uint64_t* __restrict__ nonces,
+                                                        const uint8_t* __restrict__ blocks_in,
+                                                        uint8_t* __restrict__ blocks_out,
+                                                        uint64_t* __restrict__ tokens_out,
+                                                        uint64_t* __restrict__ nonces_out, uint64_t eos_token,
+                                                        KeyTableDev kt) {
   __shared__ uint32_t tab[256];
   __shared__ uint8_t isb[256];
-  for (uint32_t i = threadIdx.x; i < 256u; i += blockDim.x) {
-    tab[i] = DECRYPT ? c_aes.td0[i] : c_aes.te0[i];
-    isb[i] = c_aes.inv_sbox[i];
-  }
-  __syncthreads();
-  for (uint32_t b = blockIdx.x; b < n_chunks; b += gridDim.x) {
-    // The segment of chunk b, chunk_base[lo] <= b < chunk_base[hi] throughout,
-    // by a 64-way search: lane l tests split point lo + l * step; chunk_base
-    // increases (every segment has a chunk), so the lanes that pass form a
-    // prefix, lane 0 always among them, and the last of them bounds the next
-    // interval.  Two rounds of loads for 4,096 segments instead of twelve.
-    uint32_t lo = 0, hi = n_segs;
-    while (hi - lo > 1u) {
-      const uint32_t step = (hi - lo + 63u) / 64u;
-      const uint32_t p = lo + threadIdx.x * step;
-      const unsigned long long pass = __ballot(p < hi && chunk_base[p] <= b);
-      lo += (63u - (uint32_t)__clzll(pass)) * step;
-      hi = min(hi, lo + step);
+  static_assert(kTokenChunk == 64, "one wave per workgroup: a round-key word per lane");
+  const uint32_t lane = threadIdx.x;
+  for (uint32_t b = blockIdx.x; b < n_runs; b += gridDim.x) {
+    const uint32_t rv = held(lane < 4u ? ((const uint32_t*)(runs + b))[lane] : 0u);
+    if (b == blockIdx.x) {  // while the first record is on its way
+      for (uint32_t i = lane; i < 256u; i += kTokenChunk) {
+        tab[i] = DECRYPT ? c_aes.td0[i] : c_aes.te0[i];
+        if (DECRYPT) isb[i] = c_aes.inv_sbox[i];
+      }
+      __syncthreads();
     }
-    const uint32_t s = lo;
-    const uint64_t rb = segs[s].row_begin, rc = segs[s].row_count;
-    const uint32_t user = segs[s].user;
-    const uint64_t i = (uint64_t)kTokenChunk * (b - chunk_base[s]) + threadIdx.x;
-    const uint32_t keys = held((DECRYPT ? kt.dk : kt.rk)[64ull * user + threadIdx.x]);
-    static_assert(kTokenChunk == 64, "one wave per chunk: a round-key word per lane");
-    if (i < rc) {
-      const uint64_t r = rb + i;
+    const uint64_t row = (uint64_t)lane_word(rv, 1) << 32 | lane_word(rv, 0);
+    const uint32_t user = lane_word(rv, 2), count = lane_word(rv, 3);
+    const uint32_t keys = held((DECRYPT ? kt.dk : kt.rk)[64ull * user + lane]);
+    for (uint32_t i = lane; i < count; i += kTokenChunk) {
+      const uint64_t r = row + i;
       if (!DECRYPT) {
         const uint64_t t = tokens[r], n = nonces[r];
         uint32_t o[4];
@@ -1567,13 +1560,13 @@ __global__ __launch_bounds__(kTokenChunk) void k_tokens(const SegDesc* __restric
         }
         *(uint4*)(blocks_out + 16ull * r) = make_uint4(o[0], o[1], o[2], o[3]);
       } else {
-        const uint4 b = *(const uint4*)(blocks_in + 16ull * r);
+        const uint4 c = *(const uint4*)(blocks_in + 16ull * r);
         uint64_t t, n;
-        if ((b.x & b.y & b.z & b.w) == 0xFFFFFFFFu) {
+        if ((c.x & c.y & c.z & c.w) == 0xFFFFFFFFu) {
           t = eos_token;
           n = 0;
         } else {
-          const uint32_t blk[4] = {b.x, b.y, b.z, b.w};
+          const uint32_t blk[4] = {c.x, c.y, c.z, c.w};
           uint32_t p[4];
           aes256_decrypt_tab(keys, blk, p, tab, isb);
           t = (uint64_t)p[0] | ((uint64_t)p[1] << 32);
@@ -1764,18 +1757,17 @@ hipError_t launch_zero_ranges(uint8_t* out, const ZeroRange* r, uint32_t n, cons
   return hipGetLastError();
 }
 
-hipError_t launch_tokens(const SegDesc* segs, const uint32_t* chunk_base, uint32_t n_segs, uint32_t n_chunks,
-                         bool decrypt, const uint64_t* tokens, const uint64_t* nonces, const uint8_t* blocks_in,
-                         uint8_t* blocks_out, uint64_t* tokens_out, uint64_t* nonces_out, uint64_t eos_token,
-                         KeyTableDev kt, hipStream_t s) {
-  if (n_segs == 0 || n_chunks == 0) return hipSuccess;
-  const uint32_t grid = n_chunks < 65535u ? n_chunks : 65535u;
+hipError_t launch_tokens(const TokenRun* runs, uint32_t n_runs, bool decrypt, const uint64_t* tokens,
+                         const uint64_t* nonces, const uint8_t* blocks_in, uint8_t* blocks_out, uint64_t* tokens_out,
+                         uint64_t* nonces_out, uint64_t eos_token, KeyTableDev kt, hipStream_t s) {
+  if (n_runs == 0) return hipSuccess;
+  const uint32_t grid = n_runs < 65535u ? n_runs : 65535u;
   if (decrypt)
-    hipLaunchKernelGGL(k_tokens<true>, dim3(grid), dim3(kTokenChunk), 0, s, segs, chunk_base, n_segs, n_chunks,
-                       tokens, nonces, blocks_in, blocks_out, tokens_out, nonces_out, eos_token, kt);
+    hipLaunchKernelGGL(k_tokens<true>, dim3(grid), dim3(kTokenChunk), 0, s, runs, n_runs, tokens, nonces, blocks_in,
+                       blocks_out, tokens_out, nonces_out, eos_token, kt);
   else
-    hipLaunchKernelGGL(k_tokens<false>, dim3(grid), dim3(kTokenChunk), 0, s, segs, chunk_base, n_segs, n_chunks,
-                       tokens, nonces, blocks_in, blocks_out, tokens_out, nonces_out, eos_token, kt);
+    hipLaunchKernelGGL(k_tokens<false>, dim3(grid), dim3(kTokenChunk), 0, s, runs, n_runs, tokens, nonces, blocks_in,
+                       blocks_out, tokens_out, nonces_out, eos_token, kt);
   return hipGetLastError();
 }
 
