@@ -42,7 +42,7 @@ size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 // What the host decides for a call's launches, from per-segment counts only
 // (the tile tables and the work queue are built on the device by
 // launch_expand): the queue's capacity, the tile kernel's grid and whether
-// the finalize pass may have work.
+// some segment may have more than one entry (finalize: its entries' sums meet).
 struct QueuePlan {
   uint64_t cap = 0;
   uint32_t grid = 0;
@@ -88,10 +88,10 @@ TilePlan plan_tiles(uint32_t n_tiles, uint64_t tile_rows_all, uint32_t n_multi, 
   // most: 8 waves multiply sooner than 16 (11 rows: 29.4 / 27.9).
   if (n_tiles > cus ? tile_rows_all <= (uint64_t)kTwoTeamRows * n_tiles : tile_rows_all <= cus) t.teams = 2;
   t.workers = n_tiles > cus ? t.teams * cus : cus;
-  // A call of one-tile segments needs no finalize pass while no tile is cut.
-  // A row takes a team about 5 us, the finalize pass about 5 us of stream time
-  // and, on open, the zeroing pass behind it 4 us more, so a cut that shortens
-  // the longest tile by fewer than two rows (three on open) does not pay.
+  // While no tile of a call of one-tile segments is cut, no sums need to meet.
+  // A row takes a team about 5 us, the meeting of a segment's pieces about as
+  // much and, on open, the zeroing pass 4 us more, so a cut that shortens the
+  // longest tile by fewer than two rows (three on open) does not pay.
   // With one worker no tile of up to kPieceRows rows is cut (and the queue is
   // as long as the tiles, with nothing to pad).
   const uint64_t p = (tile_rows_all + t.workers - 1) / t.workers;
@@ -743,7 +743,7 @@ gift_status run_gcm(const gift_tensor* t, const gift_segment_table* st, gift_key
 
   // scratch: the staged tables (descs | brief records | zero ranges | queue
   // head), then what the device builds and fills (tile_base | small list |
-  // segment values | cut marks | work queue | partials | verdicts | one-tile tag masks)
+  // segment values | work queue | partials and rows done | verdicts | tag masks)
   const size_t o_desc = 0;
   const size_t o_br = o_desc + align256(sizeof(SegDesc) * n);
   const size_t o_zr = o_br + align256(sizeof(SegBrief) * (n + 1));
@@ -752,10 +752,9 @@ gift_status run_gcm(const gift_tensor* t, const gift_segment_table* st, gift_key
   const size_t o_tb = o_st;
   const size_t o_sl = o_tb + align256(4ull * (n + 1));
   const size_t o_si = o_sl + align256(4ull * (n ? n : 1));
-  const size_t o_sc = o_si + align256(sizeof(SegInfo) * (n ? n : 1));
-  const size_t o_to = o_sc + align256(4ull * (n ? n : 1));
+  const size_t o_to = o_si + align256(sizeof(SegInfo) * (n ? n : 1));
   const size_t o_pt = o_to + align256(sizeof(TileEnt) * (Q.cap ? Q.cap : 1));
-  const size_t o_vd = o_pt + align256(16ull * (P.n_tiles ? P.n_tiles : 1));
+  const size_t o_vd = o_pt + align256(16ull * (P.n_tiles ? P.n_tiles : 1)) + align256(4ull * (n ? n : 1));
   const size_t o_fn = o_vd + align256(4ull * (n ? n : 1));
   const size_t bytes = o_fn + align256(16ull * (n ? n : 1));
   ScratchLease lease;
@@ -789,9 +788,12 @@ gift_status run_gcm(const gift_tensor* t, const gift_segment_table* st, gift_key
   // zeroes the tile partials (pieces of a cut tile XOR theirs into them) and
   // expands the segment table on the device
   const ExpandArgs ex{(uint32_t*)(scratch + o_tb), (uint32_t*)(scratch + o_sl), (TileEnt*)(scratch + o_to),
-                      (uint32_t)Q.cap, TP.workers, nullptr, (SegInfo*)(scratch + o_si), (uint32_t*)(scratch + o_sc),
-                      kSmallMaxBlocks};
+                      (uint32_t)Q.cap, TP.workers, nullptr, (SegInfo*)(scratch + o_si), nullptr, kSmallMaxBlocks};
   const SegDesc* d_desc = (const SegDesc*)(scratch + o_desc);
+  // zeroed together where a segment may have several entries: the tile
+  // partials, and behind them the rows done of each segment
+  uint32_t* seg_rows = (uint32_t*)(scratch + o_pt + 16ull * P.n_tiles);
+  const uint32_t n_zero = Q.finalize ? P.n_tiles + (n + 3u) / 4u : 0u;
   gift_status rs = GIFT_OK;
   EventMark call_ev;  // the event recorded behind the call's last kernel
   // the call's kernels after the prologue, enqueued while the staging slot is
@@ -807,16 +809,14 @@ gift_status run_gcm(const gift_tensor* t, const gift_segment_table* st, gift_key
       a.chunk_shift = 0;
       a.segs = d_desc;
       a.n_segs = n;
-      a.tile_base = (const uint32_t*)(scratch + o_tb);
       a.small_list = (const uint32_t*)(scratch + o_sl);
       a.n_tiles = P.n_tiles;
       a.n_ents = (uint32_t)Q.cap;
       a.n_small = P.n_small;
-      a.n_multi = Q.finalize ? 1u : 0u;
       a.partials = (uint4*)(scratch + o_pt);
       a.fin = (const uint4*)(scratch + o_fn);
       a.tile_order = (const TileEnt*)(scratch + o_to);
-      a.seg_cut = (const uint32_t*)(scratch + o_sc);
+      a.seg_rows = seg_rows;
       a.tile_counter = (uint32_t*)(scratch + o_qh);
       a.any_failed = a.tile_counter + 1;
       a.verdicts = verdicts;
@@ -843,13 +843,11 @@ gift_status run_gcm(const gift_tensor* t, const gift_segment_table* st, gift_key
         }
       }
       e = launch_gcm_small(a, OPEN, stream);
-      if (e == hipSuccess) e = launch_gcm_finalize(a, OPEN, stream);
       // open: segments that failed are zeroed after their verdicts are known;
-      // without a finalize pass every verdict came from a kernel that zeroed
-      // its own failed segments (the small-segment kernel, or the tile kernel
-      // for an uncut one-tile segment)
+      // where no segment has several entries, each was zeroed by the kernel
+      // that found it (the small-segment kernel, or the tile kernel)
       if (e == hipSuccess && OPEN && Q.finalize)
-        e = launch_zero_failed(a.any_failed, d_desc, n, a.tile_base, P.n_tiles, verdicts, nullptr, (uint8_t*)out, 0u, cus,
+        e = launch_zero_failed(a.any_failed, d_desc, n, ex.tile_base, P.n_tiles, verdicts, nullptr, (uint8_t*)out, 0u, cus,
                                stream);
       if (e != hipSuccess) {
         rs = hip_fail(e, "gcm launch");
@@ -870,7 +868,7 @@ gift_status run_gcm(const gift_tensor* t, const gift_segment_table* st, gift_key
       scratch, host.data(), o_st, stream,
       [&](const void* src) {
         hipError_t r = launch_prologue(scratch, src, o_st, n, t->n_rows, kNoBids, st->row_labels, n ? verdicts : nullptr,
-                                       &kt->dev, (uint4*)(scratch + o_fn), (uint4*)(scratch + o_pt), P.n_tiles, o_br,
+                                       &kt->dev, (uint4*)(scratch + o_fn), (uint4*)(scratch + o_pt), n_zero, o_br,
                                        n ? &ex : nullptr, nullptr, stream);
         if (r != hipSuccess) {
           rs = hip_fail(r, "prologue launch");
@@ -1018,7 +1016,7 @@ gift_status run_paged(const gift_paged_kv* kv, const gift_request* reqs, uint32_
 
   // scratch: the staged tables (descs | brief records | block ids | queue
   // head), then what the device builds and fills (tile_base | small list |
-  // segment values | cut marks | work queue | partials | verdicts | chunk offsets | one-tile tag masks)
+  // segment values | work queue | partials and rows done | verdicts | chunk offsets | tag masks)
   const size_t o_desc = 0;
   const size_t o_br = o_desc + align256(sizeof(SegDesc) * n);
   const size_t o_bid = o_br + align256(sizeof(SegBrief) * (n + 1));
@@ -1027,10 +1025,9 @@ gift_status run_paged(const gift_paged_kv* kv, const gift_request* reqs, uint32_
   const size_t o_tb = o_st;
   const size_t o_sl = o_tb + align256(4ull * (n + 1));
   const size_t o_si = o_sl + align256(4ull * n);
-  const size_t o_sc = o_si + align256(sizeof(SegInfo) * n);
-  const size_t o_to = o_sc + align256(4ull * n);
+  const size_t o_to = o_si + align256(sizeof(SegInfo) * n);
   const size_t o_pt = o_to + align256(sizeof(TileEnt) * (Q.cap ? Q.cap : 1));
-  const size_t o_vd = o_pt + align256(16ull * (n_tiles ? n_tiles : 1));
+  const size_t o_vd = o_pt + align256(16ull * (n_tiles ? n_tiles : 1)) + align256(4ull * n);
   const size_t o_ck = o_vd + align256(4ull * n);
   const size_t o_fn = o_ck + align256(8ull * cpos);
   const size_t bytes = o_fn + align256(16ull * (n ? n : 1));
@@ -1056,11 +1053,15 @@ gift_status run_paged(const gift_paged_kv* kv, const gift_request* reqs, uint32_
   // the prologue copies the tables, settles the verdicts (owner check by
   // block id), zeroes the tile partials and expands the segment table
   const ExpandArgs ex{(uint32_t*)(scratch + o_tb), (uint32_t*)(scratch + o_sl), (TileEnt*)(scratch + o_to),
-                      (uint32_t)Q.cap, TP.workers, nullptr, (SegInfo*)(scratch + o_si), (uint32_t*)(scratch + o_sc), 0u};
+                      (uint32_t)Q.cap, TP.workers, nullptr, (SegInfo*)(scratch + o_si), nullptr, 0u};
   gift_status rs = GIFT_OK;
   EventMark call_ev;  // the event recorded behind the call's last kernel
   const SegDesc* d_desc = (const SegDesc*)(scratch + o_desc);
   uint64_t* d_ck = (uint64_t*)(scratch + o_ck);
+  // zeroed together where a segment may have several entries: the tile
+  // partials, and behind them the rows done of each segment
+  uint32_t* seg_rows = (uint32_t*)(scratch + o_pt + 16ull * n_tiles);
+  const uint32_t n_zero = Q.finalize ? n_tiles + (n + 3u) / 4u : 0u;
   const ChunkTable chunks{d_ck, cpos, per_block_chunks, kv->layer_stride, kv->block_stride, kv->part_stride, kv->n_parts};
   // the call's kernels after the prologue, enqueued while the staging slot is
   // held (one event behind the last of them frees the slot)
@@ -1073,16 +1074,14 @@ gift_status run_paged(const gift_paged_kv* kv, const gift_request* reqs, uint32_
     a.chunk_shift = shift;
     a.segs = d_desc;
     a.n_segs = n;
-    a.tile_base = (const uint32_t*)(scratch + o_tb);
     a.small_list = (const uint32_t*)(scratch + o_sl);
     a.n_tiles = n_tiles;
     a.n_ents = (uint32_t)Q.cap;
-    a.n_multi = Q.finalize ? 1u : 0u;
     a.n_small = 0;
     a.partials = (uint4*)(scratch + o_pt);
     a.fin = (const uint4*)(scratch + o_fn);
     a.tile_order = (const TileEnt*)(scratch + o_to);
-    a.seg_cut = (const uint32_t*)(scratch + o_sc);
+    a.seg_rows = seg_rows;
     a.tile_counter = (uint32_t*)(scratch + o_qh);
     a.any_failed = a.tile_counter + 1;
     a.verdicts = verdicts;
@@ -1098,7 +1097,6 @@ gift_status run_paged(const gift_paged_kv* kv, const gift_request* reqs, uint32_
     }
     e = launch_gcm_tiles(a, OPEN ? (kModeOpen | kModeScatter) : kModeGather, TP.grid, TP.teams, stream);
     if (e == hipSuccess && g_prof_after) e = hipEventRecord(g_prof_after, stream);
-    if (e == hipSuccess) e = launch_gcm_finalize(a, OPEN, stream);
     if (e == hipSuccess && OPEN)
       e = launch_zero_failed(a.any_failed, d_desc, n, (const uint32_t*)(scratch + o_tb), n_tiles, verdicts, d_ck,
                              (uint8_t*)kv->base, shift, cus, stream);
@@ -1111,7 +1109,7 @@ gift_status run_paged(const gift_paged_kv* kv, const gift_request* reqs, uint32_
   e = sg ? sg->upload(scratch, host.data(), o_st, stream,
                       [&](const void* src) {
                         hipError_t r = launch_prologue(scratch, src, o_st, n, total_bids, o_bid, labels, verdicts, &kt->dev,
-                                                       (uint4*)(scratch + o_fn), (uint4*)(scratch + o_pt), n_tiles,
+                                                       (uint4*)(scratch + o_fn), (uint4*)(scratch + o_pt), n_zero,
                                                        o_br, &ex, &chunks, stream);
                         if (r != hipSuccess) {
                           rs = hip_fail(r, "prologue launch");

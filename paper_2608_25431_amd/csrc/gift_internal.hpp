@@ -24,12 +24,11 @@ constexpr uint32_t kTileBlocks = (uint32_t)kThreads * kRows;  // 2 MiB per tile 
 static_assert(kThreads % 64 == 0 && kThreads <= 1024, "workgroup size");
 constexpr uint32_t kSmallMaxBlocks = 64;                   // segments up to 1 KiB: one wave each
 constexpr int kHxLanes = 64;                               // H * x^(64+k), k < 64, per user
-constexpr int kFinLanes = 64;                              // lanes of the per-segment finalize
+constexpr int kFinLanes = 64;                              // lanes of the fold over a segment's tiles
 constexpr int kHPowers = kThreads + 2;                     // H^0 .. H^(kThreads+1) per user
 
 // kSegOneTile: a tiled segment of at most kTileBlocks blocks; unless its tile
-// is cut into pieces, the tile kernel writes its tag (open: its verdict)
-// itself and the finalize pass skips it.
+// is cut into pieces, its tag needs no other entry's sum.
 enum : uint32_t { kSegAligned = 1u, kSegSmall = 2u, kSegOneTile = 4u };
 
 // Device descriptor of one segment (64 B), built on the host.
@@ -98,16 +97,14 @@ struct GcmArgs {
   uint32_t chunk_shift;
   const SegDesc* segs;
   uint32_t n_segs;
-  const uint32_t* tile_base;   // [n_segs + 1] first tile of each segment (small ones: 0 tiles)
   const uint32_t* small_list;  // [n_small] indices of small segments
   uint32_t n_tiles;
   uint32_t n_ents;             // capacity of the work queue (tiles, some cut into pieces; kNoTile after the last)
   uint32_t n_small;
-  uint32_t n_multi;            // nonzero: launch the finalize pass (some segment may have more than one entry)
   uint4* partials;             // [n_tiles] GHASH partial of each tile
   const uint4* fin;            // [n_segs] E_K(J0) xor H*L of tiled segments (from the prologue)
   const TileEnt* tile_order;   // [n_ents] tiles and pieces in the order the workgroups claim them
-  const uint32_t* seg_cut;     // [n_segs] 1: a one-tile segment cut into pieces (the finalize pass forms its tag)
+  uint32_t* seg_rows;          // [n_segs] rows done of segments of several entries (zeroed by the prologue)
   uint32_t* tile_counter;      // work-queue head, zeroed with the staged tables
   uint32_t* any_failed;        // open: set when a tag failed and the zeroing pass has work; zeroed with the tables
   int32_t* verdicts;           // [n_segs]
@@ -164,7 +161,7 @@ struct ExpandArgs {
   uint32_t cus;
   uint32_t* n_ents;
   SegInfo* info;      // [n] scratch, used when the call has more segments than the expansion keeps in LDS
-  uint32_t* seg_cut;  // [n] out: 1 for a one-tile segment whose tile is cut (its tag comes from the finalize pass)
+  uint32_t* seg_cut;  // [n] out: 1 for a one-tile segment whose tile is cut, else 0 (or NULL)
   uint32_t small_max;  // blocks of the largest small segment (0: the call has no small-segment path)
 };
 // First kernel of a call.  Copies bytes of staged tables from src (the
@@ -205,7 +202,6 @@ inline uint64_t queue_capacity(uint32_t n_tiles, uint32_t cus) {
 // grid workgroups of one or two teams (see plan_tiles)
 hipError_t launch_gcm_tiles(const GcmArgs& a, int mode, uint32_t grid, uint32_t teams, hipStream_t s);
 hipError_t launch_gcm_small(const GcmArgs& a, bool open, hipStream_t s);
-hipError_t launch_gcm_finalize(const GcmArgs& a, bool open, hipStream_t s);
 hipError_t launch_zero_ranges(uint8_t* out, const ZeroRange* r, uint32_t n, const int32_t* verdicts, uint32_t grid,
                               hipStream_t s);
 hipError_t launch_wipe(void* p, size_t bytes, hipStream_t s);

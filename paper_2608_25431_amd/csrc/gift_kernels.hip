@@ -19,11 +19,11 @@
 // sum into the tile's; the last wave of the team to do so finishes the tile,
 // while the others are in the next one.  The expansion cuts some tiles into
 // row pieces (every tile when a call has fewer tiles than teams, else up to
-// one per team at the queue's tail), whose partials meet by XOR.
+// one per team at the queue's tail), whose partials meet by XOR.  The wave that
+// completes a segment's rows folds its tiles and writes its tag.
 //
 // Around it: k_prologue (first kernel of a call: staged tables from pinned
-// host memory, owner check, E_K(J0) xor H*L of one-tile segments),
-// k_finalize (tags of longer segments), k_small (segments up to 1 KiB),
+// host memory, owner check, E_K(J0) xor H*L), k_small (segments up to 1 KiB),
 // zero-fill, the paged-call helpers, per-token encryption and key setup.
 #include <hip/hip_runtime.h>
 
@@ -49,7 +49,7 @@ struct TileInfo {
   uint32_t g, s, trow, user;  // queue entry
   int32_t verdict;
   uint32_t pad[3];
-  uint4 fin;  // one-tile segment: E_K(J0) xor H*L from the prologue
+  uint4 fin;  // E_K(J0) xor H*L of its segment, from the prologue
   SegDesc desc;
   uint32_t rk[64];  // round keys (60 used)
 };
@@ -358,6 +358,68 @@ __device__ __noinline__ u128 wave_sum_of(u128 y, u128 hp) {
   return z;
 }
 
+// The lane's index (the thread index would be an argument of an out-of-line
+// function, held in a register throughout its caller).
+__device__ __forceinline__ uint32_t lane_index() {
+  return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+}
+// gf_mul_wave out of line, for the same reason as wave_sum_of.
+__device__ __noinline__ u128 wave_mul(u128 x, u128 y) { return gf_mul_wave(x, y, lane_index()); }
+
+// Tiles of a segment of m blocks.
+__device__ __forceinline__ uint32_t tiles_in(uint32_t nblocks) {
+  return (uint32_t)(((uint64_t)nblocks + kTileBlocks - 1) / kTileBlocks);
+}
+
+// Rows of tile t of a segment of m blocks (tiles aligned to its end: only the
+// first tile, t = tiles - 1, can be partial).
+__device__ __forceinline__ uint32_t tile_rows_of(uint32_t m, uint32_t t) {
+  const int64_t base = (int64_t)m - (int64_t)(t + 1) * (int64_t)kTileBlocks;
+  return base >= 0 ? (uint32_t)kRows : (uint32_t)kRows - (uint32_t)((uint64_t)(-base) / kThreads);
+}
+
+// sum_t P_t H^(tT) over the nt tile partials of a segment, by one wave: lane l
+// folds tiles l, l + 64, ...; with up to four tiles, 16 lanes share a tile's
+// product.  ht: H^(lT) of lane l; hlt: H^(64T).  The partials were written by
+// other workgroups of this launch, so they are read past the caches.
+//
+// It runs in the tile kernel, by the wave that completes the segment.  As a
+// kernel of its own behind the tile kernel it took 4.0 us for one segment of 8
+// tiles, nearly all of it the launch.
+__device__ __noinline__ u128 fold_tiles(const uint32_t* partials, uint32_t nt, const uint4* ht, const uint4* hlt) {
+  const uint32_t lane = lane_index();
+  auto part = [&](uint32_t t) -> u128 {
+    u128 v;
+#pragma unroll
+    for (int j = 0; j < 4; j++)
+      v.w[j] = __hip_atomic_load(partials + 4ull * t + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return v;
+  };
+  u128 z = u128_zero();
+  if (nt <= 4u) {
+    const uint32_t t = lane >> 4;
+    if (t < nt) {
+      const u128 x = part(t);
+      if (t > 0u)
+        z = gf_mul_slice(x, ld_u128(ht + t), lane & 15u);
+      else if (lane == 0u)
+        z = x;
+    }
+  } else if (lane < nt) {
+    const uint32_t K = (nt - 1 - lane) / kFinLanes + 1;
+    const u128 hl = ld_u128(ht + lane);
+    z = part(lane + (K - 1) * kFinLanes);
+    if (K > 1) {
+      const u128 h64 = ld_u128(hlt);
+      for (int k = (int)K - 2; k >= 0; k--) z = u128_xor(gf_mul(z, h64), part(lane + (uint32_t)k * kFinLanes));
+    }
+    if (lane > 0) z = gf_mul(z, hl);
+  }
+#pragma unroll
+  for (int j = 0; j < 4; j++) z.w[j] = wave_xor(z.w[j]);
+  return z;
+}
+
 // ---------------------------------------------------------------------------
 // Per-block kernel over 2 MiB tiles of the non-small segments.
 // ---------------------------------------------------------------------------
@@ -382,7 +444,7 @@ __global__ __launch_bounds__(kThreads) void k_gcm_tiles(GcmArgs a) {
     t->rk[l] = a.kt.rk[(size_t)e.user * 64u + l];
     if (l < 16u) ((uint32_t*)&t->desc)[l] = ((const uint32_t*)(a.segs + e.s))[l];
     if (l == 16u) t->verdict = a.verdicts[e.s];
-    if (l == 17u) t->fin = a.fin[e.s];  // meaningful for one-tile segments only
+    if (l == 17u) t->fin = a.fin[e.s];
   };
   // the tables of M of a user, by one wave: two calls, so that the loads can
   // be in flight while the team finishes with the tables before them
@@ -464,13 +526,11 @@ __global__ __launch_bounds__(kThreads) void k_gcm_tiles(GcmArgs a) {
   for (uint32_t k = 0;; k++) {
     wave_wait(&ts->rec, k + 1u);
     const TileInfo* ti = &ts->info[k % kSlots];
-    const uint32_t g = __builtin_amdgcn_readfirstlane(ti->g);
-    if (g == kNoTile) break;
+    if ((uint32_t)__builtin_amdgcn_readfirstlane(ti->g) == kNoTile) break;
     // the thread index, recomputed per tile: per-lane values derived from it
     // are formed here, not hoisted to the kernel's start and held (or
     // spilled) across every tile
     const uint32_t tid_t = opaque(tid) % kTeamThreads;
-    const uint32_t s = __builtin_amdgcn_readfirstlane(ti->s);
     const uint32_t trow = __builtin_amdgcn_readfirstlane(ti->trow);
     const uint32_t t = trow & 0xFFFFu;                                      // tile of the segment
     // its rows in this entry, in the team's rows
@@ -479,9 +539,6 @@ __global__ __launch_bounds__(kThreads) void k_gcm_tiles(GcmArgs a) {
     const int32_t verdict = (int32_t)__builtin_amdgcn_readfirstlane((uint32_t)ti->verdict);
     const uint32_t m = __builtin_amdgcn_readfirstlane(ti->desc.nblocks);
     const uint64_t off = uniform64(ti->desc.byte_off), len = uniform64(ti->desc.len);
-    const uint32_t flags = __builtin_amdgcn_readfirstlane(ti->desc.flags);
-    // a one-tile segment whose tile is cut into pieces gets its tag from the finalize pass
-    const bool one = (flags & kSegOneTile) != 0 && r0 == 0 && r1 == kTeamRows;
     const int64_t base = (int64_t)m - (int64_t)(t + 1) * (int64_t)kTileBlocks;  // block index of virtual slot 0
     const int r_start = base < 0 ? (int)((uint64_t)(-base) / kTeamThreads) : 0;
     const int r_lo = r_start > r0 ? r_start : r0;
@@ -629,117 +686,76 @@ __global__ __launch_bounds__(kThreads) void k_gcm_tiles(GcmArgs a) {
     }
     if (wave_arrive(&sum->done) != kTeamWaves - 1u) continue;
 
-    // the last wave of the team finishes the tile (fold, one and the row range
-    // are wave-uniform); lane 0 writes
-    bool failed = false;
-    if (fold) {
-      u128 p = u128{{sum->z[0], sum->z[1], sum->z[2], sum->z[3]}};
-      if (r0 == 0 && r1 == kTeamRows) {
-        if (!one && lane == 0) st_u128(a.partials + g, p);
-      } else {
-        // a piece of a cut tile: its lane powers assumed rows up to the
-        // tile's end, so it still carries H^(kTeamThreads * (kTeamRows - r1));
-        // pieces meet in the tile's (zeroed) partial by XOR
-        if (r1 < kTeamRows)
-          p = gf_mul_wave(p, ld_u128(a.kt.pow_hr + (size_t)user * kRows + (kTeamRows - r1) / TEAMS), lane);
-        if (lane == 0) {
-          uint32_t* dst = (uint32_t*)(a.partials + g);
-          for (int j = 0; j < 4; j++) atomicXor(dst + j, p.w[j]);
-        }
-      }
-      if (one) {
-        // S = P_0 xor H*L, tag = E_K(J0) xor S (the finalize pass skips this segment)
-        const u128 tag = u128_xor(p, u128{{ti->fin.x, ti->fin.y, ti->fin.z, ti->fin.w}});
-        if (!OPEN) {
-          uint32_t* to = (uint32_t*)(a.tags_out + 16ull * s);
-          if (lane == 0)
-            for (int j = 0; j < 4; j++) to[j] = tag.w[j];
-        } else {
-          const uint32_t* tin = (const uint32_t*)(a.tags_in + 16ull * s);
-          uint32_t diff = 0;
-          for (int j = 0; j < 4; j++) diff |= tin[j] ^ tag.w[j];
-          failed = __builtin_amdgcn_readfirstlane(diff) != 0;
-          if (lane == 0) a.verdicts[s] = failed ? kVerdictAuthFail : kVerdictOk;
-          if (SCATTER && failed && lane == 0) *a.any_failed = 1u;
-        }
-      }
-    } else if (one && !OPEN && lane == 0) {
-      uint32_t* to = (uint32_t*)(a.tags_out + 16ull * s);  // rejected: zero tag
-      for (int j = 0; j < 4; j++) to[j] = 0u;
-    }
-    // open of a contiguous tensor: a one-tile segment whose tag failed
-    // releases zeros only.  Its tile is the whole segment, so it is zeroed
-    // here, after every wave's rows (multi-tile and cut segments are zeroed by
-    // a later pass once the finalize pass has their verdicts).
-    if (OPEN && !GATHER && !SCATTER && failed) {
-      const uint32_t z = opaque(0u);
-      for (uint64_t i = lane; i < m; i += 64u) {
-        const uint64_t rem = len - 16ull * i;
-        store_block(a.out + off + 16ull * i, u128{{z, z, z, z}}, rem >= 16 ? 16u : (uint32_t)rem);
-      }
-    }
-    if (lane < 8u) ((uint32_t*)sum)[lane] = 0u;  // free for tile k + kSlots
+    // The last wave of the team finishes the tile; lane 0 writes.  What only
+    // this part needs of the record is read here, not held across the rows.
+    const uint32_t g = __builtin_amdgcn_readfirstlane(ti->g), s = __builtin_amdgcn_readfirstlane(ti->s);
+    const uint32_t m_e = __builtin_amdgcn_readfirstlane(ti->desc.nblocks);
+    const uint32_t trow_e = __builtin_amdgcn_readfirstlane(ti->trow), t_e = trow_e & 0xFFFFu;
+    const uint32_t p0 = (trow_e >> 16) & 0xFFu, p1 = trow_e >> 24;  // its rows, of kThreads blocks
+    const uint32_t flags = __builtin_amdgcn_readfirstlane(ti->desc.flags);
+    const uint32_t user_e = __builtin_amdgcn_readfirstlane(ti->user);
+    const uint64_t off_e = uniform64(ti->desc.byte_off), len_e = uniform64(ti->desc.len);
+    const bool one = (flags & kSegOneTile) != 0 && p0 == 0u && p1 == (uint32_t)kRows;  // the tile is the whole segment
+    u128 p = u128{{sum->z[0], sum->z[1], sum->z[2], sum->z[3]}};
+    const u128 fin = u128{{ti->fin.x, ti->fin.y, ti->fin.z, ti->fin.w}};
+    if (lane < 8u) ((uint32_t*)sum)[lane] = 0u;  // the slot is free for tile k + kSlots
     wave_set(&ts->fin, k + 1u);
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Per-segment finalize of tiled segments: S = sum_t P_t H^(tT) xor H*L and
-// tag = E_K(J0) xor S, of which the prologue has formed E_K(J0) xor H*L.  One
-// wave per segment; lane l folds tiles l, l+64, ...; with up to four tiles, 16
-// lanes share a tile's product.  Bound by latency: three dependent loads, then
-// a product.  With E_K(J0) and H*L formed here:
-// one 16 MiB segment 5.8 us, now 4.0; 16 segments of up to 128 tiles 10.8, now
-// 6.4.
-// ---------------------------------------------------------------------------
-template <bool OPEN>
-__global__ __launch_bounds__(kFinLanes) void k_finalize(GcmArgs a) {
-  const uint32_t s = blockIdx.x, lane = threadIdx.x;
-  const SegDesc sd = ld_uniform(a.segs + s);
-  const uniform_ptr tbs = to_uniform(a.tile_base + s);
-  const uint32_t cut = to_uniform(a.seg_cut + s)[0], tb = tbs[0], nt = tbs[1] - tb;
-  const int32_t verdict = (int32_t)to_uniform((const uint32_t*)a.verdicts + s)[0];
-  if ((sd.flags & kSegSmall) || ((sd.flags & kSegOneTile) && !cut)) return;
-  if (verdict != kVerdictOk) {
-    if (!OPEN && lane < 4) ((uint32_t*)(a.tags_out + 16ull * s))[lane] = 0u;
-    return;
-  }
-  const uint32_t user = sd.user;
-  const u128 fin = ld_u128(a.fin + s);
-  u128 z = u128_zero();
-  if (nt <= 4u) {
-    const uint32_t t = lane >> 4;
-    if (t < nt) {
-      const u128 x = ld_u128(a.partials + tb + t);
-      if (t > 0u)
-        z = gf_mul_slice(x, ld_u128(a.kt.pow_ht + (size_t)user * kFinLanes + t), lane & 15u);
-      else if (lane == 0u)
-        z = x;
+    if (!fold) {
+      if (!OPEN && lane < 4u) ((uint32_t*)(a.tags_out + 16ull * s))[lane] = 0u;  // rejected: zero tag
+      continue;
     }
-  } else if (lane < nt) {
-    const uint32_t K = (nt - 1 - lane) / kFinLanes + 1;
-    const u128 ht = ld_u128(a.kt.pow_ht + (size_t)user * kFinLanes + lane);
-    z = ld_u128(a.partials + tb + lane + (K - 1) * kFinLanes);
-    if (K > 1) {
-      const u128 hlt = ld_u128(a.kt.pow_hlt + user);
-      for (int k = (int)K - 2; k >= 0; k--)
-        z = u128_xor(gf_mul(z, hlt), ld_u128(a.partials + tb + lane + (uint32_t)k * kFinLanes));
+    if (!one) {
+      // A piece of a cut tile: its lane powers assumed rows up to the tile's
+      // end, so it still carries H^(kThreads * (kRows - p1)); pieces
+      // meet in the tile's (zeroed) partial by XOR.
+      if (p1 < (uint32_t)kRows) p = wave_mul(p, ld_u128(a.kt.pow_hr + (size_t)user_e * kRows + (kRows - p1)));
+      if (lane < 4u) {
+        uint32_t* dst = (uint32_t*)(a.partials + g) + lane;
+        const uint32_t v = lane == 0u ? p.w[0] : lane == 1u ? p.w[1] : lane == 2u ? p.w[2] : p.w[3];
+        if (p0 == 0u && p1 == (uint32_t)kRows)
+          __hip_atomic_store(dst, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else
+          __hip_atomic_fetch_xor(dst, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      // The entry that completes the segment's rows forms its tag.  The partials
+      // are written and read by device-scope atomics, past the XCDs' caches, so
+      // that the write above need only be complete before the rows count it.
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+      __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+      const uint32_t nt = tiles_in(m_e), all = (nt - 1u) * kRows + tile_rows_of(m_e, nt - 1u);
+      const uint32_t lo = kRows - tile_rows_of(m_e, t_e), mine = p1 - (p0 > lo ? p0 : lo);
+      uint32_t before = 0;
+      if (lane == 0u)
+        before = __hip_atomic_fetch_add(a.seg_rows + s, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if ((uint32_t)__builtin_amdgcn_readfirstlane(before) + mine != all) continue;
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+      p = fold_tiles((const uint32_t*)(a.partials + (g - t_e)), nt, a.kt.pow_ht + (size_t)user_e * kFinLanes,
+                     a.kt.pow_hlt + user_e);
     }
-    if (lane > 0) z = gf_mul(z, ht);
-  }
-#pragma unroll
-  for (int j = 0; j < 4; j++) z.w[j] = wave_xor(z.w[j]);
-  const u128 tag = u128_xor(fin, z);
-  if (lane == 0) {
+    // S = sum_t P_t H^(tT) xor H*L, tag = E_K(J0) xor S
+    const u128 tag = u128_xor(p, fin);
     if (!OPEN) {
-      store_block(a.tags_out + 16ull * s, tag, 16u);
-    } else {
-      const u128 want = load_block(a.tags_in + 16ull * s, 16u);
-      uint32_t diff = 0;
+      if (lane == 0) store_block(a.tags_out + 16ull * s, tag, 16u);
+      continue;
+    }
+    const u128 want = load_block(a.tags_in + 16ull * s, 16u);
+    uint32_t diff = 0;
 #pragma unroll
-      for (int k = 0; k < 4; k++) diff |= want.w[k] ^ tag.w[k];
-      a.verdicts[s] = diff ? kVerdictAuthFail : kVerdictOk;
-      if (diff) *a.any_failed = 1u;
+    for (int j = 0; j < 4; j++) diff |= want.w[j] ^ tag.w[j];
+    const bool failed = __builtin_amdgcn_readfirstlane(diff) != 0;
+    if (lane == 0) a.verdicts[s] = failed ? kVerdictAuthFail : kVerdictOk;
+    if (!failed) continue;
+    // Open of a contiguous tensor: a segment of one uncut tile whose tag failed
+    // releases zeros only.  Its tile is the whole segment, so it is zeroed here,
+    // after every wave's rows.  The others are zeroed by a later pass.
+    if (SCATTER || !one) {
+      if (lane == 0) *a.any_failed = 1u;
+    } else {
+      const uint32_t z = opaque(0u);
+      for (uint64_t i = lane; i < m_e; i += 64u) {
+        const uint64_t rem = len_e - 16ull * i;
+        store_block(a.out + off_e + 16ull * i, u128{{z, z, z, z}}, rem >= 16 ? 16u : (uint32_t)rem);
+      }
     }
   }
 }
@@ -845,8 +861,7 @@ __global__ __launch_bounds__(64) void k_small(GcmArgs a) {
 //     than kPieceRows rows (in tile order within a row count), is cut into
 //     pieces of kPieceRows rows.  Pieces are aligned to the tile's end; the
 //     lowest may start below the tile's first row.  A one-tile segment
-//     whose tile is cut is marked in seg_cut (its tag comes from the
-//     finalize pass);
+//     whose tile is cut is marked in seg_cut;
 //   - the work queue: every whole tile and every piece, longest first (a
 //     counting sort by the rows an entry runs), padded with kNoTile up to
 //     cap entries.
@@ -863,17 +878,6 @@ constexpr int kPrologueThreads = kExpandThreads;  // the most; 256 for tables th
 // AES block takes (16 per workgroup made 1024 segments' prologue 2.4 us longer).
 constexpr uint32_t kPrologueWaves = 4;
 constexpr uint32_t kRunTiles = 16;
-
-__device__ __forceinline__ uint32_t tiles_in(uint32_t nblocks) {
-  return (uint32_t)(((uint64_t)nblocks + kTileBlocks - 1) / kTileBlocks);
-}
-
-// Rows of tile t of a segment of m blocks (tiles aligned to its end: only the
-// first tile, t = tiles - 1, can be partial).
-__device__ __forceinline__ uint32_t tile_rows_of(uint32_t m, uint32_t t) {
-  const int64_t base = (int64_t)m - (int64_t)(t + 1) * (int64_t)kTileBlocks;
-  return base >= 0 ? (uint32_t)kRows : (uint32_t)kRows - (uint32_t)((uint64_t)(-base) / kThreads);
-}
 
 // Inclusive prefix sum over the wave's 64 lanes on the VALU's data-parallel
 // primitives (no LDS round trips): row shifts by 1, 2, 4 and 8 scan each row
@@ -986,7 +990,7 @@ __device__ bool expand_short(const SegBrief* brief, uint32_t n, const ExpandArgs
   const uint32_t part_pieces = part_cut ? r / p : 0u, part_len = part_cut ? r % p : part ? r : 0u;
   if (have) {
     x.tile_base[tid] = tb;
-    x.seg_cut[tid] = nt == 1u && (nc || part_cut) ? 1u : 0u;
+    if (x.seg_cut) x.seg_cut[tid] = nt == 1u && (nc || part_cut) ? 1u : 0u;
     if (small) x.small_list[sm] = tid;
   }
   if (tid == 0u) x.tile_base[n] = n_tiles;
@@ -1066,7 +1070,8 @@ __device__ bool expand_short(const SegBrief* brief, uint32_t n, const ExpandArgs
 
 // Expansion by the calling workgroup (all its threads call it), from the
 // per-segment brief records (the source may be host memory).  A one-tile
-// segment whose tile is cut gets seg_cut = 1 (every segment gets its 0 or 1).
+// segment whose tile is cut gets seg_cut = 1 (every segment gets its 0 or 1,
+// where seg_cut is given).
 // The per-segment values the walks need sit in LDS for up to kInfoLds
 // segments, else in x.info.
 constexpr uint32_t kInfoLds = 1024;
@@ -1098,7 +1103,7 @@ __device__ void expand_tables(const SegBrief* brief, uint32_t n, const ExpandArg
       info[i].m = m;
       info[i].flags = small ? kSegSmall : (m <= kTileBlocks ? kSegOneTile : 0u);
       info[i].user = user;
-      x.seg_cut[i] = 0u;
+      if (x.seg_cut) x.seg_cut[i] = 0u;
     };
     for (uint32_t i0 = tid; i0 < n16; i0 += kInFlight * nt_) {
       uint4 q[kInFlight];
@@ -1315,7 +1320,7 @@ __device__ void expand_tables(const SegBrief* brief, uint32_t n, const ExpandArg
       }
     }
     // a one-tile segment has one run: this thread owns its entry
-    if ((v.flags & kSegOneTile) && (q.nc || q.part_cut)) x.seg_cut[s] = 1u;
+    if (x.seg_cut && (v.flags & kSegOneTile) && (q.nc || q.part_cut)) x.seg_cut[s] = 1u;
   });
   uint3 tot2;
   const uint3 b2 = block_scan3(make_uint3(my_full, my_pieces, 0u), wsum3, &tot2);
@@ -1737,15 +1742,6 @@ hipError_t launch_gcm_small(const GcmArgs& a, bool open, hipStream_t s) {
     hipLaunchKernelGGL(k_small<true>, dim3(a.n_small), dim3(64), 0, s, a);
   else
     hipLaunchKernelGGL(k_small<false>, dim3(a.n_small), dim3(64), 0, s, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_gcm_finalize(const GcmArgs& a, bool open, hipStream_t s) {
-  if (a.n_multi == 0) return hipSuccess;
-  if (open)
-    hipLaunchKernelGGL(k_finalize<true>, dim3(a.n_segs), dim3(kFinLanes), 0, s, a);
-  else
-    hipLaunchKernelGGL(k_finalize<false>, dim3(a.n_segs), dim3(kFinLanes), 0, s, a);
   return hipGetLastError();
 }
 
