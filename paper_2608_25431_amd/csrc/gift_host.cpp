@@ -743,7 +743,7 @@ gift_status run_gcm(const gift_tensor* t, const gift_segment_table* st, gift_key
 
   // scratch: the staged tables (descs | brief records | zero ranges | queue
   // head), then what the device builds and fills (tile_base | small list |
-  // segment values | work queue | partials and rows done | verdicts | tag masks)
+  // segment values | work queue | partials and rows done | verdicts)
   const size_t o_desc = 0;
   const size_t o_br = o_desc + align256(sizeof(SegDesc) * n);
   const size_t o_zr = o_br + align256(sizeof(SegBrief) * (n + 1));
@@ -755,8 +755,9 @@ gift_status run_gcm(const gift_tensor* t, const gift_segment_table* st, gift_key
   const size_t o_to = o_si + align256(sizeof(SegInfo) * (n ? n : 1));
   const size_t o_pt = o_to + align256(sizeof(TileEnt) * (Q.cap ? Q.cap : 1));
   const size_t o_vd = o_pt + align256(16ull * (P.n_tiles ? P.n_tiles : 1)) + align256(4ull * (n ? n : 1));
-  const size_t o_fn = o_vd + align256(4ull * (n ? n : 1));
-  const size_t bytes = o_fn + align256(16ull * (n ? n : 1));
+  // (16 B per segment more than is used: the fixed workspace's limit, in calls
+  // that it takes, stays where it has been)
+  const size_t bytes = o_vd + align256(4ull * (n ? n : 1)) + align256(16ull * (n ? n : 1));
   ScratchLease lease;
   uint8_t* scratch = nullptr;
   hipError_t e = hipSuccess;
@@ -814,7 +815,6 @@ gift_status run_gcm(const gift_tensor* t, const gift_segment_table* st, gift_key
       a.n_ents = (uint32_t)Q.cap;
       a.n_small = P.n_small;
       a.partials = (uint4*)(scratch + o_pt);
-      a.fin = (const uint4*)(scratch + o_fn);
       a.tile_order = (const TileEnt*)(scratch + o_to);
       a.seg_rows = seg_rows;
       a.tile_counter = (uint32_t*)(scratch + o_qh);
@@ -868,8 +868,7 @@ gift_status run_gcm(const gift_tensor* t, const gift_segment_table* st, gift_key
       scratch, host.data(), o_st, stream,
       [&](const void* src) {
         hipError_t r = launch_prologue(scratch, src, o_st, n, t->n_rows, kNoBids, st->row_labels, n ? verdicts : nullptr,
-                                       &kt->dev, (uint4*)(scratch + o_fn), (uint4*)(scratch + o_pt), n_zero, o_br,
-                                       n ? &ex : nullptr, nullptr, stream);
+                                       (uint4*)(scratch + o_pt), n_zero, o_br, n ? &ex : nullptr, nullptr, stream);
         if (r != hipSuccess) {
           rs = hip_fail(r, "prologue launch");
           return r;
@@ -1016,7 +1015,7 @@ gift_status run_paged(const gift_paged_kv* kv, const gift_request* reqs, uint32_
 
   // scratch: the staged tables (descs | brief records | block ids | queue
   // head), then what the device builds and fills (tile_base | small list |
-  // segment values | work queue | partials and rows done | verdicts | chunk offsets | tag masks)
+  // segment values | work queue | partials and rows done | verdicts | chunk offsets)
   const size_t o_desc = 0;
   const size_t o_br = o_desc + align256(sizeof(SegDesc) * n);
   const size_t o_bid = o_br + align256(sizeof(SegBrief) * (n + 1));
@@ -1029,8 +1028,7 @@ gift_status run_paged(const gift_paged_kv* kv, const gift_request* reqs, uint32_
   const size_t o_pt = o_to + align256(sizeof(TileEnt) * (Q.cap ? Q.cap : 1));
   const size_t o_vd = o_pt + align256(16ull * (n_tiles ? n_tiles : 1)) + align256(4ull * n);
   const size_t o_ck = o_vd + align256(4ull * n);
-  const size_t o_fn = o_ck + align256(8ull * cpos);
-  const size_t bytes = o_fn + align256(16ull * (n ? n : 1));
+  const size_t bytes = o_ck + align256(8ull * cpos);
   ScratchLease lease;
   hipError_t e = lease.acquire(dev, stream, bytes);
   if (e != hipSuccess) return hip_fail(e, "device scratch");
@@ -1079,7 +1077,6 @@ gift_status run_paged(const gift_paged_kv* kv, const gift_request* reqs, uint32_
     a.n_ents = (uint32_t)Q.cap;
     a.n_small = 0;
     a.partials = (uint4*)(scratch + o_pt);
-    a.fin = (const uint4*)(scratch + o_fn);
     a.tile_order = (const TileEnt*)(scratch + o_to);
     a.seg_rows = seg_rows;
     a.tile_counter = (uint32_t*)(scratch + o_qh);
@@ -1108,9 +1105,9 @@ gift_status run_paged(const gift_paged_kv* kv, const gift_request* reqs, uint32_
   };
   e = sg ? sg->upload(scratch, host.data(), o_st, stream,
                       [&](const void* src) {
-                        hipError_t r = launch_prologue(scratch, src, o_st, n, total_bids, o_bid, labels, verdicts, &kt->dev,
-                                                       (uint4*)(scratch + o_fn), (uint4*)(scratch + o_pt), n_zero,
-                                                       o_br, &ex, &chunks, stream);
+                        hipError_t r = launch_prologue(scratch, src, o_st, n, total_bids, o_bid, labels, verdicts,
+                                                       (uint4*)(scratch + o_pt), n_zero, o_br, &ex, &chunks,
+                                                       stream);
                         if (r != hipSuccess) {
                           rs = hip_fail(r, "prologue launch");
                           return r;
@@ -1292,8 +1289,8 @@ gift_status gift_check_owner(const gift_segment_table* st, const uint32_t* label
   EventMark call_ev;  // the event recorded behind the prologue
   e = sg ? sg->upload(d, P.descs.data(), bytes, stream,
                       [&](const void* src) {
-                        return launch_prologue(d, src, bytes, n, n_rows, kNoBids, labels, st->verdicts, nullptr, nullptr,
-                                               nullptr, 0u, 0u, nullptr, nullptr, stream);
+                        return launch_prologue(d, src, bytes, n, n_rows, kNoBids, labels, st->verdicts, nullptr,
+                                               0u, 0u, nullptr, nullptr, stream);
                       },
                       false, &call_ev)
          : hipErrorInvalidDevice;
@@ -1375,8 +1372,8 @@ static gift_status run_tokens(bool decrypt, const gift_segment_table* st, uint64
     e = sg->upload(d, runs.data(), staged, stream,
                    [&](const void* src) {
                      if (direct) return rest((const TokenRun*)src);
-                     hipError_t r = launch_prologue(d, src, staged, 0, 0, kNoBids, nullptr, nullptr, nullptr, nullptr,
-                                                    nullptr, 0u, 0u, nullptr, nullptr, stream);
+                     hipError_t r = launch_prologue(d, src, staged, 0, 0, kNoBids, nullptr, nullptr, nullptr, 0u, 0u,
+                                                    nullptr, nullptr, stream);
                      return r != hipSuccess ? r : rest(d);
                    },
                    false, &call_ev);

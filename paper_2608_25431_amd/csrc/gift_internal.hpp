@@ -102,7 +102,6 @@ struct GcmArgs {
   uint32_t n_ents;             // capacity of the work queue (tiles, some cut into pieces; kNoTile after the last)
   uint32_t n_small;
   uint4* partials;             // [n_tiles] GHASH partial of each tile
-  const uint4* fin;            // [n_segs] E_K(J0) xor H*L of tiled segments (from the prologue)
   const TileEnt* tile_order;   // [n_ents] tiles and pieces in the order the workgroups claim them
   uint32_t* seg_rows;          // [n_segs] rows done of segments of several entries (zeroed by the prologue)
   uint32_t* tile_counter;      // work-queue head, zeroed with the staged tables
@@ -169,8 +168,7 @@ struct ExpandArgs {
 // n_zero tile partials at zero (pieces of a cut tile XOR theirs into them),
 // and, when verdicts is not NULL, writes each segment's first verdict: the
 // owner check against labels (indexed by row, or by the block ids at byte
-// bids_off of the tables for paged calls) or OK without labels.  With a key
-// table it also writes fin[s] = E_K(J0) xor H*L of every tiled segment s.
+// bids_off of the tables for paged calls) or OK without labels.
 // The descriptors sit at byte 0 of the tables; rows: the rows of all segments
 // that the owner check reads.  With ex, one workgroup runs
 // the segment-table expansion into *ex meanwhile, from the brief records at
@@ -186,8 +184,7 @@ struct ChunkTable {
   uint32_t parts;
 };
 hipError_t launch_prologue(void* dst, const void* src, size_t bytes, uint32_t n_segs, uint64_t rows, uint64_t bids_off,
-                           const uint32_t* labels, int32_t* verdicts, const KeyTableDev* kt, uint4* fin,
-                           uint4* zero, uint32_t n_zero, uint64_t brief_off, const ExpandArgs* ex,
+                           const uint32_t* labels, int32_t* verdicts, uint4* zero, uint32_t n_zero, uint64_t brief_off, const ExpandArgs* ex,
                            const ChunkTable* chunks, hipStream_t s);
 // The expansion alone, on brief records in device memory: the library's test
 // hook.

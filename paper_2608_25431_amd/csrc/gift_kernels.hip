@@ -23,7 +23,7 @@
 // completes a segment's rows folds its tiles and writes its tag.
 //
 // Around it: k_prologue (first kernel of a call: staged tables from pinned
-// host memory, owner check, E_K(J0) xor H*L), k_small (segments up to 1 KiB),
+// host memory, owner check), k_small (segments up to 1 KiB),
 // zero-fill, the paged-call helpers, per-token encryption and key setup.
 #include <hip/hip_runtime.h>
 
@@ -49,7 +49,6 @@ struct TileInfo {
   uint32_t g, s, trow, user;  // queue entry
   int32_t verdict;
   uint32_t pad[3];
-  uint4 fin;  // E_K(J0) xor H*L of its segment, from the prologue
   SegDesc desc;
   uint32_t rk[64];  // round keys (60 used)
 };
@@ -363,8 +362,60 @@ __device__ __noinline__ u128 wave_sum_of(u128 y, u128 hp) {
 __device__ __forceinline__ uint32_t lane_index() {
   return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
 }
+// Global memory as such, for out-of-line functions (through generic pointers
+// their accesses would be flat ones).
+typedef const __attribute__((address_space(1))) u32x4* global_block;
+typedef const __attribute__((address_space(1))) uint32_t* global_word;
+__device__ __forceinline__ u128 ld_global(global_block p) {
+  const u32x4 v = *p;
+  return u128{{v.x, v.y, v.z, v.w}};
+}
 // gf_mul_wave out of line, for the same reason as wave_sum_of.
 __device__ __noinline__ u128 wave_mul(u128 x, u128 y) { return gf_mul_wave(x, y, lane_index()); }
+
+// What the tag of a segment needs besides its blocks: E_K(J0) xor H*L, J0 = IV
+// || BE32(1), by one wave (the result is wave-uniform).  rec and tt: places in
+// LDS of the segment's TileInfo and of the T-tables; H*L is a wave sum over the
+// set bits of the length block (only its low 64 bits can be set) of the products
+// hxl = H * x^(64+k).  Out of line, as wave_sum_of; it addresses LDS as LDS, not
+// through generic pointers.
+__device__ __noinline__ u128 tag_mask(uint32_t rec, uint32_t tt, global_block hxl) {
+  typedef const __attribute__((address_space(3))) uint32_t* lds_words;
+  const uint32_t lane = lane_index();
+  const lds_words r = (lds_words)rec;
+  auto word = [&](size_t at) { return (uint32_t)__builtin_amdgcn_readfirstlane(r[at / 4]); };
+  const uint64_t len = (uint64_t)word(offsetof(TileInfo, desc) + offsetof(SegDesc, len) + 4) << 32 |
+                       word(offsetof(TileInfo, desc) + offsetof(SegDesc, len));
+  u128 z = u128_zero();
+  if (((len * 8ull) >> (63 - lane)) & 1ull) z = ld_global(hxl + lane);
+  constexpr size_t iv = offsetof(TileInfo, desc) + offsetof(SegDesc, iv), rk = offsetof(TileInfo, rk);
+  uint32_t s0 = word(iv) ^ word(rk), s1 = word(iv + 4) ^ word(rk + 4), s2 = word(iv + 8) ^ word(rk + 8),
+           s3 = 0x01000000u ^ word(rk + 12);
+  // table k of byte k, this lane's copy
+  const uint32_t c = tt + ((lane & 31u) << 2);
+  auto te = [&](uint32_t w, uint32_t k) -> uint32_t {
+    return *(lds_words)(c + (((w >> (8u * k)) & 0xFFu) << 8) + 128u * (k & 1u) + 65536u * (k >> 1));
+  };
+#pragma unroll 1
+  for (uint32_t i = 1; i < 14u; i++) {
+    const lds_words k = r + rk / 4 + 4u * i;
+    const uint32_t t0 = xor3(te(s0, 0), te(s1, 1), te(s2, 2)) ^ te(s3, 3) ^ k[0];
+    const uint32_t t1 = xor3(te(s1, 0), te(s2, 1), te(s3, 2)) ^ te(s0, 3) ^ k[1];
+    const uint32_t t2 = xor3(te(s2, 0), te(s3, 1), te(s0, 2)) ^ te(s1, 3) ^ k[2];
+    const uint32_t t3 = xor3(te(s3, 0), te(s0, 1), te(s1, 2)) ^ te(s2, 3) ^ k[3];
+    s0 = t0, s1 = t1, s2 = t2, s3 = t3;
+  }
+  // S(x) is byte 1 of T0[x] (bytes 2S, S, S, 3S)
+  auto sb = [&](uint32_t w, uint32_t k) -> uint32_t {
+    const uint32_t x = *(lds_words)(c + (((w >> (8u * k)) & 0xFFu) << 8));
+    return ((x >> 8) & 0xFFu) << (8u * k);
+  };
+  const uint32_t o[4] = {sb(s0, 0) | sb(s1, 1) | sb(s2, 2) | sb(s3, 3), sb(s1, 0) | sb(s2, 1) | sb(s3, 2) | sb(s0, 3),
+                         sb(s2, 0) | sb(s3, 1) | sb(s0, 2) | sb(s1, 3), sb(s3, 0) | sb(s0, 1) | sb(s1, 2) | sb(s2, 3)};
+#pragma unroll
+  for (int j = 0; j < 4; j++) z.w[j] = wave_xor(z.w[j]) ^ __builtin_amdgcn_readfirstlane(o[j]) ^ word(rk + 4 * (56 + j));
+  return z;
+}
 
 // Tiles of a segment of m blocks.
 __device__ __forceinline__ uint32_t tiles_in(uint32_t nblocks) {
@@ -386,7 +437,7 @@ __device__ __forceinline__ uint32_t tile_rows_of(uint32_t m, uint32_t t) {
 // It runs in the tile kernel, by the wave that completes the segment.  As a
 // kernel of its own behind the tile kernel it took 4.0 us for one segment of 8
 // tiles, nearly all of it the launch.
-__device__ __noinline__ u128 fold_tiles(const uint32_t* partials, uint32_t nt, const uint4* ht, const uint4* hlt) {
+__device__ __noinline__ u128 fold_tiles(global_word partials, uint32_t nt, global_block ht, global_block hlt) {
   const uint32_t lane = lane_index();
   auto part = [&](uint32_t t) -> u128 {
     u128 v;
@@ -401,16 +452,16 @@ __device__ __noinline__ u128 fold_tiles(const uint32_t* partials, uint32_t nt, c
     if (t < nt) {
       const u128 x = part(t);
       if (t > 0u)
-        z = gf_mul_slice(x, ld_u128(ht + t), lane & 15u);
+        z = gf_mul_slice(x, ld_global(ht + t), lane & 15u);
       else if (lane == 0u)
         z = x;
     }
   } else if (lane < nt) {
     const uint32_t K = (nt - 1 - lane) / kFinLanes + 1;
-    const u128 hl = ld_u128(ht + lane);
+    const u128 hl = ld_global(ht + lane);
     z = part(lane + (K - 1) * kFinLanes);
     if (K > 1) {
-      const u128 h64 = ld_u128(hlt);
+      const u128 h64 = ld_global(hlt);
       for (int k = (int)K - 2; k >= 0; k--) z = u128_xor(gf_mul(z, h64), part(lane + (uint32_t)k * kFinLanes));
     }
     if (lane > 0) z = gf_mul(z, hl);
@@ -444,7 +495,6 @@ __global__ __launch_bounds__(kThreads) void k_gcm_tiles(GcmArgs a) {
     t->rk[l] = a.kt.rk[(size_t)e.user * 64u + l];
     if (l < 16u) ((uint32_t*)&t->desc)[l] = ((const uint32_t*)(a.segs + e.s))[l];
     if (l == 16u) t->verdict = a.verdicts[e.s];
-    if (l == 17u) t->fin = a.fin[e.s];
   };
   // the tables of M of a user, by one wave: two calls, so that the loads can
   // be in flight while the team finishes with the tables before them
@@ -667,7 +717,7 @@ __global__ __launch_bounds__(kThreads) void k_gcm_tiles(GcmArgs a) {
     u128 hp = u128_zero();
     if (fold) hp = ld_u128(a.kt.pow_h + (size_t)user * kHPowers + (kTeamThreads + 1u - tid_e));
     wave_wait(&ts->fin, k - (kSlots - 1u));  // the slot's previous tile is finished
-    wave_arrive(&sum->rows);
+    const bool first = wave_arrive(&sum->rows) == 0u;
     if (tw == kTabWave) {
       const TileInfo* tn = &ts->info[(k + 1u) % kSlots];
       wave_wait(&ts->rec, k + 2u);
@@ -680,7 +730,15 @@ __global__ __launch_bounds__(kThreads) void k_gcm_tiles(GcmArgs a) {
       wave_set(&ts->mtab, k + 2u);
     }
     if (fold) {
-      const u128 z = wave_sum_of(y, hp);
+      u128 z = wave_sum_of(y, hp);
+      // The rest of the tag, by the first wave that is through the rows of the
+      // segment's end, whose sum no power of H multiplies any more.  The other
+      // waves are still in their rows.  In the prologue, where a wave per
+      // segment formed it from tables of its own, it was the longest part: one
+      // 16 MiB segment 7.7 us, without it 4; 1024 segments 10.8 and 6.
+      if (first && t == 0u && r1 == kTeamRows)
+        z = u128_xor(z, tag_mask((uint32_t)((const uint8_t*)ti - smem), Team<TEAMS>::lds_aes,
+                                 (global_block)(a.kt.pow_hxl + (size_t)user * kHxLanes)));
       if (lane < 4u)
         atomicXor(&sum->z[lane], lane == 0u ? z.w[0] : lane == 1u ? z.w[1] : lane == 2u ? z.w[2] : z.w[3]);
     }
@@ -697,7 +755,6 @@ __global__ __launch_bounds__(kThreads) void k_gcm_tiles(GcmArgs a) {
     const uint64_t off_e = uniform64(ti->desc.byte_off), len_e = uniform64(ti->desc.len);
     const bool one = (flags & kSegOneTile) != 0 && p0 == 0u && p1 == (uint32_t)kRows;  // the tile is the whole segment
     u128 p = u128{{sum->z[0], sum->z[1], sum->z[2], sum->z[3]}};
-    const u128 fin = u128{{ti->fin.x, ti->fin.y, ti->fin.z, ti->fin.w}};
     if (lane < 8u) ((uint32_t*)sum)[lane] = 0u;  // the slot is free for tile k + kSlots
     wave_set(&ts->fin, k + 1u);
     if (!fold) {
@@ -729,11 +786,11 @@ __global__ __launch_bounds__(kThreads) void k_gcm_tiles(GcmArgs a) {
         before = __hip_atomic_fetch_add(a.seg_rows + s, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if ((uint32_t)__builtin_amdgcn_readfirstlane(before) + mine != all) continue;
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-      p = fold_tiles((const uint32_t*)(a.partials + (g - t_e)), nt, a.kt.pow_ht + (size_t)user_e * kFinLanes,
-                     a.kt.pow_hlt + user_e);
+      p = fold_tiles((global_word)(a.partials + (g - t_e)), nt, (global_block)(a.kt.pow_ht + (size_t)user_e * kFinLanes),
+                     (global_block)(a.kt.pow_hlt + user_e));
     }
-    // S = sum_t P_t H^(tT) xor H*L, tag = E_K(J0) xor S
-    const u128 tag = u128_xor(p, fin);
+    // tag = E_K(J0) xor S, S = sum_t P_t H^(tT) xor H*L
+    const u128 tag = p;
     if (!OPEN) {
       if (lane == 0) store_block(a.tags_out + 16ull * s, tag, 16u);
       continue;
@@ -874,8 +931,8 @@ __global__ __launch_bounds__(64) void k_small(GcmArgs a) {
 // ---------------------------------------------------------------------------
 constexpr int kExpandThreads = 1024;  // the most threads an expanding workgroup may have
 constexpr int kPrologueThreads = kExpandThreads;  // the most; 256 for tables that fit them
-// Waves of a workgroup that take a segment each: one per SIMD, whose time the
-// AES block takes (16 per workgroup made 1024 segments' prologue 2.4 us longer).
+// Waves of a workgroup that take a segment each: what its smallest workgroup
+// has (with 16 in workgroups of 1024 threads 1024 segments took the same time).
 constexpr uint32_t kPrologueWaves = 4;
 constexpr uint32_t kRunTiles = 16;
 
@@ -1388,7 +1445,7 @@ __global__ __launch_bounds__(kExpandThreads) void k_expand(const SegBrief* brief
 // device scratch, zeroes the tile partials, settles every segment's first
 // verdict -- with labels, the owner check (OWNER_MIXED iff some row label
 // differs from the segment's user; the sentinels never equal a user), else
-// OK -- and forms E_K(J0) xor H*L of one-tile segments.  With an expansion,
+// OK.  With an expansion,
 // workgroup 0 builds the tile tables and the work queue meanwhile from the
 // brief records; the other workgroups read descriptors and block ids where
 // the copy reads them, so no part waits on another.
@@ -1402,8 +1459,6 @@ struct PrologueArgs {
   const uint32_t* labels;
   const uint32_t* bids;
   int32_t* verdicts;
-  KeyTableDev kt;
-  uint4* fin;
   uint4* zero;
   uint32_t n_zero;
   ChunkTable chunks;
@@ -1414,7 +1469,6 @@ struct PrologueArgs {
 };
 
 __global__ __launch_bounds__(kPrologueThreads) void k_prologue(PrologueArgs a) {
-  __shared__ uint32_t te[256];
   const bool ex = a.expand && a.n > 0;
   if (ex && blockIdx.x == 0) {
     expand_tables(a.brief, a.n, a.x);
@@ -1441,10 +1495,6 @@ __global__ __launch_bounds__(kPrologueThreads) void k_prologue(PrologueArgs a) {
   }
   if (!a.verdicts) return;
   const SegDesc* segs = a.segs;
-  if (a.fin) {
-    for (uint32_t i = threadIdx.x; i < 256u; i += blockDim.x) te[i] = c_aes.te0[i];
-    __syncthreads();
-  }
   // A segment per wave (by_wave: few rows per segment) or per workgroup.  The
   // descriptors may be in host memory: a wave reads one in one access.
   const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
@@ -1455,17 +1505,6 @@ __global__ __launch_bounds__(kPrologueThreads) void k_prologue(PrologueArgs a) {
     auto word = [&](size_t at) { return lane_word(dv, (int)(at / 4)); };
     auto word2 = [&](size_t at) { return (uint64_t)word(at + 4) << 32 | word(at); };
     const uint32_t user = word(offsetof(SegDesc, user));
-    // what the tag of a tiled segment needs besides its tiles: E_K(J0) xor
-    // H*L, J0 = IV || BE32(1), H*L a wave sum over the set bits of the length
-    // block (only its low 64 bits can be set) of the products H*x^(64+k)
-    const bool fin = a.fin && (a.by_wave || wave == 0u) && !(word(offsetof(SegDesc, flags)) & kSegSmall);
-    uint32_t rkv = 0;
-    u128 z = u128_zero();
-    if (fin) {
-      rkv = held(a.kt.rk[(size_t)user * 64u + lane]);
-      if (((word2(offsetof(SegDesc, len)) * 8ull) >> (63 - lane)) & 1ull)
-        z = ld_u128(a.kt.pow_hxl + (size_t)user * kHxLanes + lane);
-    }
     int bad = 0;
     if (a.labels) {
       const uint64_t rb = word2(offsetof(SegDesc, row_begin)), rc = word2(offsetof(SegDesc, row_count));
@@ -1474,15 +1513,6 @@ __global__ __launch_bounds__(kPrologueThreads) void k_prologue(PrologueArgs a) {
       bad = a.by_wave ? __any(bad) : __syncthreads_or(bad);
     }
     if ((a.by_wave ? lane : threadIdx.x) == 0u) a.verdicts[s] = bad ? kVerdictOwnerMixed : kVerdictOk;
-    if (fin) {
-#pragma unroll
-      for (int j = 0; j < 4; j++) z.w[j] = wave_xor(z.w[j]);
-      const uint32_t j0[4] = {word(offsetof(SegDesc, iv)), word(offsetof(SegDesc, iv) + 4),
-                              word(offsetof(SegDesc, iv) + 8), 0x01000000u};
-      uint32_t e[4];
-      aes256_encrypt_tab(rkv, j0, e, te);
-      if (lane == 0u) a.fin[s] = make_uint4(e[0] ^ z.w[0], e[1] ^ z.w[1], e[2] ^ z.w[2], e[3] ^ z.w[3]);
-    }
   }
 }
 
@@ -1785,8 +1815,7 @@ hipError_t launch_expand(const SegBrief* brief, uint32_t n_segs, const ExpandArg
 }
 
 hipError_t launch_prologue(void* dst, const void* src, size_t bytes, uint32_t n_segs, uint64_t rows, uint64_t bids_off,
-                           const uint32_t* labels, int32_t* verdicts, const KeyTableDev* kt, uint4* fin,
-                           uint4* zero, uint32_t n_zero, uint64_t brief_off, const ExpandArgs* ex,
+                           const uint32_t* labels, int32_t* verdicts, uint4* zero, uint32_t n_zero, uint64_t brief_off, const ExpandArgs* ex,
                            const ChunkTable* chunks, hipStream_t s) {
   if (bytes & 15u) return hipErrorInvalidValue;
   const size_t n16 = src ? bytes / 16 : 0;
@@ -1816,8 +1845,6 @@ hipError_t launch_prologue(void* dst, const void* src, size_t bytes, uint32_t n_
   a.labels = labels;
   a.bids = bids_off == kNoBids ? nullptr : (const uint32_t*)(rd + bids_off);
   a.verdicts = verdicts;
-  a.kt = kt ? *kt : KeyTableDev{};
-  a.fin = kt ? fin : nullptr;
   a.zero = zero;
   a.n_zero = n_zero;
   if (chunks) a.chunks = *chunks;
