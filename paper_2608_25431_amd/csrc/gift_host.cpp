@@ -680,9 +680,10 @@ SegShape shape_of(uint64_t bytes) {
 }
 
 // The staged descriptors and, where given, brief records of a call's segments
-// (no IVs without a nonce base), straight into the staging ring.  Built in a vector, copied to the table and from there to
-// the ring, with the IVs byte by byte, a call on 1024 segments of 4 to 16 bytes,
-// bound by its host time, took 27.6 us, now 22.7.
+// (no IVs without a nonce base), straight into the staging ring.  Built in a
+// vector, copied to a table and from there to the ring, with the IVs byte by
+// byte, a call on 1024 segments of 4 to 16 bytes, bound by its host time, took
+// 27.6 us, now 22.7.
 void write_descs(const gift_segment* segs, uint32_t n, uint64_t row_bytes, const uint8_t* nonce_base, const void* in,
                  const void* out, SegDesc* descs, SegBrief* brief) {
   for (uint32_t i = 0; i < n; i++) {
