@@ -797,18 +797,25 @@ gift_status run_gcm(const gift_tensor* t, const gift_segment_table* st, gift_key
   const size_t o_to = o_si + align256(sizeof(SegInfo) * (n ? n : 1));
   const size_t o_pt = o_to + align256(sizeof(TileEnt) * (Q.cap ? Q.cap : 1));
   const size_t o_vd = o_pt + align256(16ull * (P.n_tiles ? P.n_tiles : 1)) + align256(4ull * (n ? n : 1));
-  // (16 B per segment more than is used: the fixed workspace's limit, in calls
-  // that it takes, stays where it has been)
-  const size_t bytes = o_vd + align256(4ull * (n ? n : 1)) + align256(16ull * (n ? n : 1));
+  const size_t bytes = o_vd + align256(4ull * (n ? n : 1));
   ScratchLease lease;
   uint8_t* scratch = nullptr;
   hipError_t e = hipSuccess;
   if (no_alloc) {
-    if (bytes > kStaticScratchBytes || o_st > Staging::kMaxStaged)
+    // Which calls fit is part of the interface, so it does not depend on how
+    // the tile kernel runs them: it goes by a queue for one worker per CU and
+    // 16 B per segment beside the tables.  The queue of a two-team call has
+    // 3 * CUs entries more, and those 16 B pay for them: two teams run more
+    // tiles than CUs of up to 16 rows on average, so at least 7 segments per 8
+    // tiles, and a table of too few segments to pay (768 for 256 CUs) is far
+    // from the limit, with at most half of it staged and 40 KB beside that.
+    const uint64_t cap1 = P.n_tiles ? queue_capacity(P.n_tiles, cus) : 1;
+    const size_t need = std::max(bytes, bytes - (o_pt - o_to) + align256(sizeof(TileEnt) * cap1) + align256(16ull * (n ? n : 1)));
+    if (need > kStaticScratchBytes || o_st > Staging::kMaxStaged)
       return fail(GIFT_E_NOMEM,
                   "gift_seal_noalloc: the call needs %zu bytes of workspace (%zu of them staged tables); the fixed "
                   "workspace holds %zu (%zu staged)",
-                  bytes, o_st, kStaticScratchBytes, Staging::kMaxStaged);
+                  need, o_st, kStaticScratchBytes, Staging::kMaxStaged);
     scratch = static_scratch(dev);
     if (!scratch) return fail(GIFT_E_INVALID, "gift_seal_noalloc: no workspace on device %d (create a key table there first)", dev);
   } else {

@@ -1,7 +1,7 @@
 """gift_seal_noalloc (the seal on the device's fixed workspace) against
 gift_seal through the C ABI: two calls in a row, the second with a smaller
 input, each bit-exact with the allocating entry point and with the oracle;
-and the size limit, rejected before anything is enqueued."""
+and the size limit, rejected before anything is enqueued, to the segment."""
 import numpy as np
 import pytest
 
@@ -101,4 +101,48 @@ def test_noalloc_rejects_a_call_beyond_the_workspace():
     gift.seal(d, n, rb, segs, kt, nb, out, tags)
     torch.cuda.synchronize()
     assert not (tags == 0xA5).all().item()
+    kt.destroy()
+
+
+def test_noalloc_limit_with_two_teams_and_a_cut():
+    # The workspace's limit in a call of many short tiles, of which a longer one
+    # is cut (two teams per workgroup, so the work queue has more entries than
+    # with one): the longest table that fits, and one more segment.
+    def need(n, n_tiles, cus):
+        def up(x):
+            return (x + 255) & ~255
+        staged = up(64 * n) + up(8 * (n + 1)) + 256
+        return (staged + up(4 * (n + 1)) + up(4 * n) + up(24 * n) + up(16 * (n_tiles + 3 * cus)) + up(16 * n_tiles) +
+                2 * up(4 * n) + up(16 * n))
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    n = 50_000
+    while need(n + 1, n + 2, cus) <= 8 << 20:
+        n += 1
+    r = np.random.default_rng(33)
+    keys = r.integers(0, 256, (8, 32), dtype=np.uint8)
+    nb = r.integers(0, 256, (8, 12), dtype=np.uint8)
+    kt = gift.KeyTable(keys)
+    for k, fits in ((n, True), (n + 1, False)):
+        rows = np.full(k, 65)
+        rows[k // 2] = 131072 + 70  # two tiles
+        n_rows = int(rows.sum())
+        segs = np.zeros(k, gift.SEGMENT_DTYPE)
+        segs["row_count"], segs["row_begin"] = rows, np.cumsum(rows) - rows
+        segs["user"], segs["iv_seq"] = np.arange(k) % 8, np.arange(k)
+        d = torch.randint(0, 256, (n_rows * 16,), dtype=torch.uint8, device=DEV)
+        out, tags = torch.zeros_like(d), torch.zeros(16 * k, dtype=torch.uint8, device=DEV)
+        if not fits:
+            with pytest.raises(gift.GiftError) as ei:
+                gift.seal_noalloc(d, n_rows, 16, segs, kt, nb, out, tags)
+            assert ei.value.status == gift.E_NOMEM
+            continue
+        gift.seal_noalloc(d, n_rows, 16, segs, kt, nb, out, tags)
+        want, want_tags = torch.empty_like(out), torch.empty_like(tags)
+        gift.seal(d, n_rows, 16, segs, kt, nb, want, want_tags)
+        assert torch.equal(out, want) and torch.equal(tags, want_tags)
+        for i in (0, k // 2, k - 1):  # and against the oracle
+            at = slice(int(segs["row_begin"][i]) * 16, int(segs["row_begin"][i] + rows[i]) * 16)
+            iv = oracle.segment_iv(nb[i % 8].tobytes(), i)
+            c, t = oracle.gcm_encrypt(keys[i % 8].tobytes(), iv, host(d[at]).tobytes())
+            assert host(out[at]).tobytes() == c and host(tags[16 * i:16 * i + 16]).tobytes() == t
     kt.destroy()
