@@ -471,6 +471,25 @@ __device__ __noinline__ u128 fold_tiles(global_word partials, uint32_t nt, globa
   return z;
 }
 
+// Zeroes len bytes (at most a tile's) at any address, by one wave.  The other
+// waves of the team are in the next tile, so the wave has to keep as many
+// stores under way as it can: whole blocks without a look at the segment's end.
+// Opens in which every tag fails, block by block with that look / so: 300
+// segments of 0.5 MiB 344 / 296 us per call, 256 of them 192 / 165, 600 of 2 MiB
+// 1826 / 1680.
+typedef __attribute__((address_space(1))) uint8_t* global_bytes;
+__device__ __noinline__ void zero_tile(global_bytes p, uint32_t len) {
+  typedef __attribute__((address_space(1))) u32x4_any* blocks;
+  const uint32_t lane = lane_index(), whole = len / 16u;
+  const blocks q = (blocks)p + lane;
+  uint32_t i = 0;
+  for (; i + 512u <= whole; i += 512u)
+#pragma unroll
+    for (uint32_t k = 0; k < 512u; k += 64u) q[i + k] = u32x4{0u, 0u, 0u, 0u};
+  for (; i + lane < whole; i += 64u) q[i] = u32x4{0u, 0u, 0u, 0u};
+  if (lane < (len & 15u)) p[16u * whole + lane] = 0;
+}
+
 // ---------------------------------------------------------------------------
 // Per-block kernel over 2 MiB tiles of the non-small segments.
 // ---------------------------------------------------------------------------
@@ -808,11 +827,7 @@ __global__ __launch_bounds__(kThreads) void k_gcm_tiles(GcmArgs a) {
     if (SCATTER || !one) {
       if (lane == 0) *a.any_failed = 1u;
     } else {
-      const uint32_t z = opaque(0u);
-      for (uint64_t i = lane; i < m_e; i += 64u) {
-        const uint64_t rem = len_e - 16ull * i;
-        store_block(a.out + off_e + 16ull * i, u128{{z, z, z, z}}, rem >= 16 ? 16u : (uint32_t)rem);
-      }
+      zero_tile((global_bytes)(a.out + off_e), (uint32_t)len_e);
     }
   }
 }

@@ -105,6 +105,15 @@ def test_one_team_fewer_tiles_than_cus(users):
     check(users, *table_of(r.choice(EDGES, n), r.integers(0, 40, n)), 16, 8)
 
 
+@pytest.mark.parametrize("row_bytes", [16, 20])
+def test_failed_tiles_are_zeroed_to_the_byte(users, row_bytes):
+    # uncut one-tile segments, two thirds of them tampered, between good ones: one wave zeroes each, 512 whole blocks
+    # at a time, then 64, then the bytes of a ragged end
+    blocks = [b + d for b in (128, 512, 576, 1024, 1536, 2048, 2560) for d in (-1, 0, 1)]
+    rows = [b * 16 // row_bytes + d for b in blocks for d in ((0,) if row_bytes == 16 else (0, 1, 2))]
+    check(users, *table_of(rows, [i % 40 for i in range(len(rows))]), row_bytes, 10, reject=1, flips=len(rows) * 2 // 3)
+
+
 def test_paged_two_teams(users):
     from test_gpu_parity import paged_case, paged_geom
     keys, nb, kt = users
