@@ -153,13 +153,8 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t v) {
 }
 __device__ __forceinline__ uniform_ptr to_uniform(const uint32_t* p) { return (uniform_ptr)uniform64((uint64_t)p); }
 
-// v, which every lane of the wave holds from here on: lane_word reads it from
-// lanes that a branch has switched off, and the compiler, which does not know
-// that, must not move v's load into the branch.
-__device__ __forceinline__ uint32_t held(uint32_t v) {
-  asm volatile("" : "+v"(v));
-  return v;
-}
+// Lane `lane`'s v, in every lane.  That lane must be active: a copy or a spill of
+// v that the compiler places inside a branch moves the active lanes' values only.
 __device__ __forceinline__ uint32_t lane_word(uint32_t v, int lane) {
   return (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
 }
@@ -169,6 +164,7 @@ __device__ __forceinline__ uint32_t lane_word(uint32_t v, int lane) {
 // constant segment): te0 as in AesConst, and S(x) is byte 1 of te0[x].  Lane l
 // of the wave holds round-key word l in rkv: one coalesced load, whose latency
 // comes before the rounds, instead of a load of each round's keys inside them.
+// Every lane of the wave must be active.
 __device__ inline void aes256_encrypt_tab(uint32_t rkv, const uint32_t in[4], uint32_t out[4], const uint32_t* te0) {
   uint32_t s0 = in[0] ^ lane_word(rkv, 0), s1 = in[1] ^ lane_word(rkv, 1), s2 = in[2] ^ lane_word(rkv, 2),
            s3 = in[3] ^ lane_word(rkv, 3);
@@ -194,7 +190,7 @@ __device__ inline void aes256_encrypt_tab(uint32_t rkv, const uint32_t in[4], ui
 }
 
 // Equivalent inverse cipher with td0 and the inverse S-box passed in; lane l of
-// the wave holds word l of its round keys in dkv.
+// the wave holds word l of its round keys in dkv.  Every lane must be active.
 __device__ inline void aes256_decrypt_tab(uint32_t dkv, const uint32_t in[4], uint32_t out[4], const uint32_t* td0,
                                           const uint8_t* isb) {
   uint32_t s0 = in[0] ^ lane_word(dkv, 56), s1 = in[1] ^ lane_word(dkv, 57), s2 = in[2] ^ lane_word(dkv, 58),

@@ -1,0 +1,72 @@
+"""Properties of the compiled kernels that no run can show, read from the gfx950 assembly of this library's sources.
+
+A lane's register read by v_readlane holds what the program put there only if the lane is active: a copy or a spill that
+the compiler places under a branch moves the active lanes' values.  The token and small-segment kernels hold one round-key
+word per lane, so they may read them only while every lane is on, whatever the compiler did this time."""
+import re
+import subprocess
+
+import pytest
+
+from paper_2608_25431_amd import build
+
+KERNELS = ["k_tokensILb0E", "k_tokensILb1E", "k_smallILb0E", "k_smallILb1E"]
+
+
+@pytest.fixture(scope="module")
+def assembly(tmp_path_factory):
+    out = tmp_path_factory.mktemp("asm") / "kernels.s"
+    cmd = ["/opt/rocm/bin/hipcc", f"--offload-arch={build.ARCH}", *build.HIP_FLAGS, "--cuda-device-only", "-S",
+           "-I", f"{build.ROOT}/include", "-I", build.CSRC, build.SOURCES[0], "-o", str(out)]
+    subprocess.run(cmd, check=True, capture_output=True, timeout=300)
+    return out.read_text().splitlines()
+
+
+def body(lines, kernel):
+    start = next(i for i, l in enumerate(lines) if re.match(rf"_ZN4gift\d+{kernel}.*:", l))
+    end = next(i for i in range(start, len(lines)) if lines[i].startswith(".Lfunc_end"))
+    return [l.split(";")[0].strip() for l in lines[start + 1:end] if l.split(";")[0].strip()]
+
+
+def masked_readlanes(code):
+    """Indices of the v_readlane instructions that some path reaches with lanes switched off.  The state is whether exec
+    is narrowed and, per scalar register pair, whether the mask saved there is; unknown masks count as narrowed."""
+    label = {l[:-1]: i for i, l in enumerate(code) if l.endswith(":")}
+    seen, found, work = {}, set(), [(0, False, frozenset())]
+    while work:
+        i, off, full = work.pop()  # full: registers that hold a whole mask
+        while i < len(code):
+            old = seen.get(i)
+            if old is not None:
+                off, full = off or old[0], full & old[1]
+                if (off, full) == old:
+                    break
+            seen[i] = (off, full)
+            op, _, args = code[i].partition(" ")
+            a = [x.strip() for x in args.split(",")]
+            if op == "v_readlane_b32" and off:
+                found.add(i)
+            elif op == "s_endpgm":
+                break
+            elif op.endswith("saveexec_b64"):
+                full = full - {a[0]} if off else full | {a[0]}
+                off = True
+            elif a[0] == "exec" and op.startswith("s_"):
+                src = a[-1]
+                off = not (op in ("s_or_b64", "s_mov_b64") and (src in full or src == "-1"))
+            elif op.startswith("s_") and a[0] in full:
+                full = full - {a[0]}
+            if op == "s_branch":
+                i = label[a[0]]
+                continue
+            if op.startswith("s_cbranch"):
+                work.append((label[a[0]], off, full))
+            i += 1
+    return found
+
+
+@pytest.mark.parametrize("kernel", KERNELS)
+def test_lanes_are_read_while_all_are_on(assembly, kernel):
+    code = body(assembly, kernel)
+    assert sum(l.startswith("v_readlane_b32") for l in code) >= 12  # the loop over the rounds keeps four of them
+    assert not masked_readlanes(code)
