@@ -1341,6 +1341,45 @@ gift_status gift_check_owner(const gift_segment_table* st, const uint32_t* label
   return GIFT_OK;
 }
 
+// Token calls of up to this many records, none of them shared, have the kernel
+// read them from the staging ring itself, a host read per workgroup; else a
+// kernel of its own copies them to device scratch first.  Sealing 64 segments of
+// 3072 tokens from the ring / from scratch with shared records 20.8 / 17.8 us per
+// call, of 4096 tokens 25.0 / 19.8; 4096 segments of one token, with nothing to
+// share, 24.1 / 28.1.
+constexpr uint64_t kDirectRuns = 4096;
+// From this many 64-token chunks on, workgroups share records where they can.
+constexpr uint64_t kShareChunks = 2048;
+
+}  // extern "C"
+
+namespace gift {
+
+// Workgroups (1 << shift) that share a record: one up to kShareChunks, then as
+// many as leave at most an eighth of the workgroups without tokens, so that the
+// table stays small beside the tokens, down to 16 records.  With longer runs for
+// fewer workgroups instead, that went through them 64 tokens at a time, calls
+// had become slower than with a search for each workgroup's segment: one of
+// 262,144 tokens in 64 segments 20.7 us with the search, 25.0 with the runs, so
+// 19.8; of 2,097,152 87.5, 92.8, 85.8; of 16,777,216 617, 648, 615.
+uint32_t token_shift(const gift_segment* segs, uint32_t n, uint64_t n_chunks) {
+  uint32_t shift = 0;
+  if (n_chunks <= kShareChunks) return shift;
+  const uint64_t most = n_chunks + n_chunks / 8;  // workgroups
+  for (uint64_t records = n_chunks; records > 16 && shift < 16; shift++) {
+    const uint32_t s = shift + 1;
+    if ((uint64_t)n << s > most) break;
+    records = 0;
+    for (uint32_t i = 0; i < n; i++) records += ((segs[i].row_count - 1) / kTokenChunk >> s) + 1;
+    if (records << s > most) break;
+  }
+  return shift;
+}
+
+}  // namespace gift
+
+extern "C" {
+
 // Per-token encryption (GIFT Sec. 4.5), both directions.
 static gift_status run_tokens(bool decrypt, const gift_segment_table* st, uint64_t n_tokens, gift_key_table kt,
                               uint64_t eos_token, const uint64_t* tokens, const uint64_t* nonces,
@@ -1365,25 +1404,20 @@ static gift_status run_tokens(bool decrypt, const gift_segment_table* st, uint64
     n_chunks += (st->segs[i].row_count + kTokenChunk - 1) / kTokenChunk;
     if (n_chunks > UINT32_MAX) return fail(GIFT_E_TOO_LARGE, "more than 2^32 - 1 chunks of %u tokens", kTokenChunk);
   }
-  // Staged: a record per run of tokens.  A run is one chunk, so that a long
-  // segment spreads over the chip; from 16384 chunks on it grows, so that the
-  // table stays small beside the tokens (each 32 B).
-  const uint64_t run_max = kTokenChunk * (n_chunks / 16384 + 1);
+  // Staged: a record per run of tokens.
+  Staging* sg = staging_for(dev);
+  if (!sg) return fail(GIFT_E_INVALID, "device index %d unsupported", dev);
+  const uint32_t shift = token_shift(st->segs, n, n_chunks);
+  const bool direct = shift == 0 && n_chunks <= kDirectRuns && sg->mapped();
+  const uint64_t run_max = (uint64_t)kTokenChunk << shift;
   std::vector<TokenRun> runs;
-  runs.reserve(n + n_chunks * kTokenChunk / run_max + 1);
+  runs.reserve(n + (n_chunks >> shift));
   for (uint32_t i = 0; i < n; i++) {
     const gift_segment& g = st->segs[i];
     for (uint64_t r = 0; r < g.row_count; r += run_max)
       runs.push_back(TokenRun{g.row_begin + r, g.user, (uint32_t)std::min(run_max, g.row_count - r)});
   }
   const size_t staged = sizeof(TokenRun) * runs.size();
-  // The kernel reads up to kDirectRuns records from the staging ring itself, a
-  // host read per workgroup that all of them make at once (about 2 us); more
-  // are copied to device scratch in whole cache lines first.
-  constexpr size_t kDirectRuns = 4096;
-  Staging* sg = staging_for(dev);
-  if (!sg) return fail(GIFT_E_INVALID, "device index %d unsupported", dev);
-  const bool direct = runs.size() <= kDirectRuns && sg->mapped();
   TokenRun* d = nullptr;
   hipError_t e = hipSuccess;
   ScratchLease lease;
@@ -1403,7 +1437,7 @@ static gift_status run_tokens(bool decrypt, const gift_segment_table* st, uint64
       r = decrypt ? launch_wipe(tokens_out, 8ull * n_tokens, stream) : launch_wipe(blocks_out, 16ull * n_tokens, stream);
     if (r == hipSuccess && gaps && decrypt && nonces_out) r = launch_wipe(nonces_out, 8ull * n_tokens, stream);
     if (r == hipSuccess)
-      r = launch_tokens(table, (uint32_t)runs.size(), decrypt, tokens, nonces, blocks_in, blocks_out, tokens_out,
+      r = launch_tokens(table, (uint32_t)runs.size(), shift, decrypt, tokens, nonces, blocks_in, blocks_out, tokens_out,
                         nonces_out, eos_token, kt->dev, stream);
     return r;
   };

@@ -210,14 +210,14 @@ hipError_t launch_zero_failed(const uint32_t* any_failed, const SegDesc* segs, u
                               const int32_t* verdicts, const uint64_t* chunk_off, uint8_t* base, uint32_t chunk_shift,
                               uint32_t grid, hipStream_t s);
 // Per-token block encryption (decrypt == true: the inverse): one record per
-// run of tokens of one segment.
+// run of up to kTokenChunk << shift tokens of one segment.
 struct TokenRun {
   uint64_t row;  // first token
   uint32_t user, count;
 };
 static_assert(sizeof(TokenRun) == 16, "TokenRun layout");
 constexpr uint32_t kTokenChunk = 64;  // tokens a workgroup takes at a time
-hipError_t launch_tokens(const TokenRun* runs, uint32_t n_runs, bool decrypt, const uint64_t* tokens,
+hipError_t launch_tokens(const TokenRun* runs, uint32_t n_runs, uint32_t shift, bool decrypt, const uint64_t* tokens,
                          const uint64_t* nonces, const uint8_t* blocks_in, uint8_t* blocks_out, uint64_t* tokens_out,
                          uint64_t* nonces_out, uint64_t eos_token, KeyTableDev kt, hipStream_t s);
 

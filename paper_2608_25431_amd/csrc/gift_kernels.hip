@@ -1586,9 +1586,10 @@ __global__ __launch_bounds__(256) void k_wipe(uint8_t* p, size_t bytes) {
 // ---------------------------------------------------------------------------
 // Per-token encryption (token || nonce as one block under the owner's key,
 // the end-of-sequence token as the all-0xFF block).  The work is cut into runs
-// of tokens of one segment, one per workgroup of 64 threads, whose records the
-// host writes (16 B: all that the kernel needs of a segment); they may be in
-// host memory.  Outputs of uncovered tokens were zeroed before this launch.
+// of tokens of one segment, whose records the host writes (16 B: all that the
+// kernel needs of a segment); they may be in host memory.  A workgroup of 64
+// threads takes 64 tokens, and 2^shift workgroups share a run.  Outputs of
+// uncovered tokens were zeroed before this launch.
 //
 // Bound by latency: the record, then keys and tokens, then 14 AES rounds.  With
 // a prologue kernel that copied the descriptors to the device and a search for
@@ -1601,6 +1602,7 @@ __global__ __launch_bounds__(256) void k_wipe(uint8_t* p, size_t bytes) {
 // ---------------------------------------------------------------------------
 template <bool DECRYPT>
 __global__ __launch_bounds__(kTokenChunk) void k_tokens(const TokenRun* __restrict__ runs, uint32_t n_runs,
+                                                        uint32_t shift,
                                                         const uint64_t* __restrict__ tokens,
                                                         const uint64_t* __restrict__ nonces,
                                                         const uint8_t* __restrict__ blocks_in,
@@ -1618,40 +1620,39 @@ __global__ __launch_bounds__(kTokenChunk) void k_tokens(const TokenRun* __restri
 #pragma unroll
   for (uint32_t k = 0; k < 4u; k++) tv[k] = (DECRYPT ? c_aes.td0 : c_aes.te0)[64u * k + lane];
   if (DECRYPT) iv = ((const uint32_t*)c_aes.inv_sbox)[lane];
-  auto record = [&](uint32_t b) { return ((const uint32_t*)(runs + b))[lane & 3u]; };
+  auto record = [&](uint64_t b) { return ((const uint32_t*)(runs + (b >> shift)))[lane & 3u]; };
   uint32_t rv = record(blockIdx.x);
 #pragma unroll
   for (uint32_t k = 0; k < 4u; k++) tab[64u * k + lane] = tv[k];
   if (DECRYPT) isb[lane] = iv;
   rv = opaque(rv);  // loaded here: not moved behind the barrier
   __syncthreads();
-  for (uint32_t b = blockIdx.x; b < n_runs; b += gridDim.x) {
+  for (uint64_t b = blockIdx.x; b < (uint64_t)n_runs << shift; b += gridDim.x) {
     if (b != blockIdx.x) rv = record(b);
     const uint64_t row = (uint64_t)lane_word(rv, 1) << 32 | lane_word(rv, 0);
     const uint32_t user = lane_word(rv, 2), count = lane_word(rv, 3);
+    const uint32_t i0 = kTokenChunk * ((uint32_t)b & ((1u << shift) - 1u)), i = i0 + lane;
+    if (i0 >= count) continue;  // the run is shorter
     const uint32_t keys = (DECRYPT ? kt.dk : kt.rk)[64ull * user + lane];
     // The rounds take their keys from all lanes, so all lanes run them, past
     // the run's end on its last token again; only the stores are masked.
-    for (uint32_t i0 = 0; i0 < count; i0 += kTokenChunk) {
-      const uint32_t i = i0 + lane;
-      const uint64_t r = row + min(i, count - 1u);
-      if (!DECRYPT) {
-        const uint64_t t = tokens[r], n = nonces[r];
-        const uint32_t blk[4] = {(uint32_t)t, (uint32_t)(t >> 32), (uint32_t)n, (uint32_t)(n >> 32)};
-        uint32_t o[4];
-        aes256_encrypt_tab(keys, blk, o, tab);
-        const uint32_t e = t == eos_token ? 0xFFFFFFFFu : 0u;
-        if (i < count) *(uint4*)(blocks_out + 16ull * r) = make_uint4(o[0] | e, o[1] | e, o[2] | e, o[3] | e);
-      } else {
-        const uint4 c = *(const uint4*)(blocks_in + 16ull * r);
-        const uint32_t blk[4] = {c.x, c.y, c.z, c.w};
-        uint32_t p[4];
-        aes256_decrypt_tab(keys, blk, p, tab, (const uint8_t*)isb);
-        const bool eos = (c.x & c.y & c.z & c.w) == 0xFFFFFFFFu;
-        if (i < count) {
-          tokens_out[r] = eos ? eos_token : (uint64_t)p[0] | ((uint64_t)p[1] << 32);
-          if (nonces_out) nonces_out[r] = eos ? 0ull : (uint64_t)p[2] | ((uint64_t)p[3] << 32);
-        }
+    const uint64_t r = row + min(i, count - 1u);
+    if (!DECRYPT) {
+      const uint64_t t = tokens[r], n = nonces[r];
+      const uint32_t blk[4] = {(uint32_t)t, (uint32_t)(t >> 32), (uint32_t)n, (uint32_t)(n >> 32)};
+      uint32_t o[4];
+      aes256_encrypt_tab(keys, blk, o, tab);
+      const uint32_t e = t == eos_token ? 0xFFFFFFFFu : 0u;
+      if (i < count) *(uint4*)(blocks_out + 16ull * r) = make_uint4(o[0] | e, o[1] | e, o[2] | e, o[3] | e);
+    } else {
+      const uint4 c = *(const uint4*)(blocks_in + 16ull * r);
+      const uint32_t blk[4] = {c.x, c.y, c.z, c.w};
+      uint32_t p[4];
+      aes256_decrypt_tab(keys, blk, p, tab, (const uint8_t*)isb);
+      const bool eos = (c.x & c.y & c.z & c.w) == 0xFFFFFFFFu;
+      if (i < count) {
+        tokens_out[r] = eos ? eos_token : (uint64_t)p[0] | ((uint64_t)p[1] << 32);
+        if (nonces_out) nonces_out[r] = eos ? 0ull : (uint64_t)p[2] | ((uint64_t)p[3] << 32);
       }
     }
   }
@@ -1826,16 +1827,17 @@ hipError_t launch_zero_ranges(uint8_t* out, const ZeroRange* r, uint32_t n, cons
   return hipGetLastError();
 }
 
-hipError_t launch_tokens(const TokenRun* runs, uint32_t n_runs, bool decrypt, const uint64_t* tokens,
+hipError_t launch_tokens(const TokenRun* runs, uint32_t n_runs, uint32_t shift, bool decrypt, const uint64_t* tokens,
                          const uint64_t* nonces, const uint8_t* blocks_in, uint8_t* blocks_out, uint64_t* tokens_out,
                          uint64_t* nonces_out, uint64_t eos_token, KeyTableDev kt, hipStream_t s) {
   if (n_runs == 0) return hipSuccess;
-  const uint32_t grid = n_runs < 65535u ? n_runs : 65535u;
+  const uint64_t n_wg = (uint64_t)n_runs << shift;
+  const uint32_t grid = n_wg < 65535u ? (uint32_t)n_wg : 65535u;
   if (decrypt)
-    hipLaunchKernelGGL(k_tokens<true>, dim3(grid), dim3(kTokenChunk), 0, s, runs, n_runs, tokens, nonces, blocks_in,
+    hipLaunchKernelGGL(k_tokens<true>, dim3(grid), dim3(kTokenChunk), 0, s, runs, n_runs, shift, tokens, nonces, blocks_in,
                        blocks_out, tokens_out, nonces_out, eos_token, kt);
   else
-    hipLaunchKernelGGL(k_tokens<false>, dim3(grid), dim3(kTokenChunk), 0, s, runs, n_runs, tokens, nonces, blocks_in,
+    hipLaunchKernelGGL(k_tokens<false>, dim3(grid), dim3(kTokenChunk), 0, s, runs, n_runs, shift, tokens, nonces, blocks_in,
                        blocks_out, tokens_out, nonces_out, eos_token, kt);
   return hipGetLastError();
 }

@@ -5,6 +5,7 @@ segment with more than one queue entry; leaving it out when a one-tile
 segment's tile is cut would leave that segment without a tag, so it must be
 launched whenever the expansion kernel's cut can reach a one-tile segment."""
 import ctypes
+import os
 import subprocess
 
 import numpy as np
@@ -20,15 +21,20 @@ class QueuePlan(ctypes.Structure):
     _fields_ = [("cap", ctypes.c_uint64), ("grid", ctypes.c_uint32), ("finalize", ctypes.c_bool)]
 
 
-@pytest.fixture(scope="module")
-def plan_queue():
-    if not __import__("os").path.exists(gift.LIB_PATH):
+def symbol(prefix):
+    """An internal function of the library, by its mangled name's prefix."""
+    if not os.path.exists(gift.LIB_PATH):
         from paper_2608_25431_amd import build
         build.build()
     lib = gift.lib()
     out = subprocess.run(["nm", "-D", "--defined-only", gift.LIB_PATH], capture_output=True, text=True).stdout
     names = [l.split()[-1] for l in out.splitlines() if l.strip()]
-    fn = getattr(lib, next(n for n in names if n.startswith("_ZN4gift10plan_queue")))
+    return getattr(lib, next(n for n in names if n.startswith(prefix)))
+
+
+@pytest.fixture(scope="module")
+def plan_queue():
+    fn = symbol("_ZN4gift10plan_queue")
     fn.argtypes = [ctypes.c_uint32, ctypes.c_uint64, ctypes.c_uint32, ctypes.c_uint32, ctypes.c_uint32]
     fn.restype = QueuePlan
     return fn
@@ -79,3 +85,35 @@ def test_examples(plan_queue):
     # more one-tile segments than CUs, longer than a quarter tile: the tail cut can reach them
     q = plan_queue(300, 300 * 96, 0, 96, 256)
     assert q.finalize and q.grid == 256
+
+
+@pytest.fixture(scope="module")
+def token_shift():
+    fn = symbol("_ZN4gift11token_shift")
+    fn.argtypes = [ctypes.c_void_p, ctypes.c_uint32, ctypes.c_uint64]
+    fn.restype = ctypes.c_uint32
+    return lambda segs, chunks: fn(segs.ctypes.data, len(segs), chunks)
+
+
+@pytest.mark.parametrize("counts", [[64 * 4096], [1] * 5000, [64 * 64] * 64, [64 * 9 - 3] * 300, [1 << 24],
+                                    [1 << 16] + [1] * 1024, [100] * 3000, [1 << 30, 1]])
+def test_token_records(token_shift, counts):
+    """Token records shared by 1 << shift workgroups of 64 tokens: at most an eighth of the workgroups find no tokens,
+    and twice as many could not share without that (or the table is small).  The work of a workgroup stays 64 tokens,
+    however long the call."""
+    segs = np.zeros(len(counts), gift.SEGMENT_DTYPE)
+    segs["row_count"] = counts
+    chunks = [-(-c // 64) for c in counts]
+
+    def records(shift):
+        return sum(-(-c // (1 << shift)) for c in chunks)
+    n = sum(chunks)
+    s = token_shift(segs, n)
+    assert records(s) << s <= n + n // 8
+    assert records(s) <= 16 or s == 16 or records(s + 1) << (s + 1) > n + n // 8
+
+
+def test_few_chunks_are_not_shared(token_shift):
+    segs = np.zeros(1, gift.SEGMENT_DTYPE)
+    segs["row_count"] = 64 * 2048
+    assert token_shift(segs, 2048) == 0

@@ -1,6 +1,6 @@
 """Per-token encryption at the edges of its work records, every block, token and nonce against the oracle: the most
 records that the kernel reads from the staging ring itself and one more (those are copied to the device first), and
-enough tokens that a record holds more than one 64-token chunk."""
+enough tokens that workgroups of 64 tokens share a record, the last of them without tokens or with a few."""
 import numpy as np
 import pytest
 
@@ -15,8 +15,11 @@ from test_gpu_parity import token_case  # noqa: E402
 @pytest.mark.parametrize("counts", [
     [1] * 4096,
     [1] * 4095 + [65],
+    [64 * 2048],
+    [64 * 2048 + 1],
+    [64 * 9 - 3] * 300,
     [64, 63, 65, 64 * 16384 - 200, 129, 1],
-], ids=["direct", "copied", "long-runs"])
+], ids=["direct", "copied", "unshared", "shared", "idle", "long"])
 def test_token_runs(counts):
     r = np.random.default_rng(len(counts))
     keys = r.integers(0, 256, (5, 32), dtype=np.uint8)
