@@ -374,15 +374,13 @@ __device__ __forceinline__ u128 ld_global(global_block p) {
 __device__ __noinline__ u128 wave_mul(u128 x, u128 y) { return gf_mul_wave(x, y, lane_index()); }
 
 // What the tag of a segment needs besides its blocks: E_K(J0) xor H*L, J0 = IV
-// || BE32(1), by one wave (the result is wave-uniform).  rec and tt: places in
-// LDS of the segment's TileInfo and of the T-tables; H*L is a wave sum over the
-// set bits of the length block (only its low 64 bits can be set) of the products
-// hxl = H * x^(64+k).  Out of line, as wave_sum_of; it addresses LDS as LDS, not
-// through generic pointers.
-__device__ __noinline__ u128 tag_mask(uint32_t rec, uint32_t tt, global_block hxl) {
-  typedef const __attribute__((address_space(3))) uint32_t* lds_words;
+// || BE32(1), by one wave (the result is wave-uniform).  r and tt: the segment's
+// TileInfo and the T-tables; H*L is a wave sum over the set bits of the length
+// block (only its low 64 bits can be set) of the products hxl = H * x^(64+k).
+// Out of line, as wave_sum_of; LDS comes as LDS pointers, not generic ones.
+typedef const __attribute__((address_space(3))) uint32_t* lds_words;
+__device__ __noinline__ u128 tag_mask(lds_words r, lds_words tt, global_block hxl) {
   const uint32_t lane = lane_index();
-  const lds_words r = (lds_words)rec;
   auto word = [&](size_t at) { return (uint32_t)__builtin_amdgcn_readfirstlane(r[at / 4]); };
   const uint64_t len = (uint64_t)word(offsetof(TileInfo, desc) + offsetof(SegDesc, len) + 4) << 32 |
                        word(offsetof(TileInfo, desc) + offsetof(SegDesc, len));
@@ -392,9 +390,9 @@ __device__ __noinline__ u128 tag_mask(uint32_t rec, uint32_t tt, global_block hx
   uint32_t s0 = word(iv) ^ word(rk), s1 = word(iv + 4) ^ word(rk + 4), s2 = word(iv + 8) ^ word(rk + 8),
            s3 = 0x01000000u ^ word(rk + 12);
   // table k of byte k, this lane's copy
-  const uint32_t c = tt + ((lane & 31u) << 2);
+  const lds_words c = tt + (lane & 31u);
   auto te = [&](uint32_t w, uint32_t k) -> uint32_t {
-    return *(lds_words)(c + (((w >> (8u * k)) & 0xFFu) << 8) + 128u * (k & 1u) + 65536u * (k >> 1));
+    return c[(((w >> (8u * k)) & 0xFFu) << 6) + 32u * (k & 1u) + 16384u * (k >> 1)];
   };
 #pragma unroll 1
   for (uint32_t i = 1; i < 14u; i++) {
@@ -407,7 +405,7 @@ __device__ __noinline__ u128 tag_mask(uint32_t rec, uint32_t tt, global_block hx
   }
   // S(x) is byte 1 of T0[x] (bytes 2S, S, S, 3S)
   auto sb = [&](uint32_t w, uint32_t k) -> uint32_t {
-    const uint32_t x = *(lds_words)(c + (((w >> (8u * k)) & 0xFFu) << 8));
+    const uint32_t x = c[((w >> (8u * k)) & 0xFFu) << 6];
     return ((x >> 8) & 0xFFu) << (8u * k);
   };
   const uint32_t o[4] = {sb(s0, 0) | sb(s1, 1) | sb(s2, 2) | sb(s3, 3), sb(s1, 0) | sb(s2, 1) | sb(s3, 2) | sb(s0, 3),
@@ -756,7 +754,7 @@ __global__ __launch_bounds__(kThreads) void k_gcm_tiles(GcmArgs a) {
       // segment formed it from tables of its own, it was the longest part: one
       // 16 MiB segment 7.7 us, without it 4; 1024 segments 10.8 and 6.
       if (first && t == 0u && r1 == kTeamRows)
-        z = u128_xor(z, tag_mask((uint32_t)((const uint8_t*)ti - smem), Team<TEAMS>::lds_aes,
+        z = u128_xor(z, tag_mask((lds_words)(const uint32_t*)ti, (lds_words)(const uint32_t*)tt,
                                  (global_block)(a.kt.pow_hxl + (size_t)user * kHxLanes)));
       if (lane < 4u)
         atomicXor(&sum->z[lane], lane == 0u ? z.w[0] : lane == 1u ? z.w[1] : lane == 2u ? z.w[2] : z.w[3]);

@@ -2,7 +2,10 @@
 
 A lane's register read by v_readlane holds what the program put there only if the lane is active: a copy or a spill that
 the compiler places under a branch moves the active lanes' values.  The token and small-segment kernels hold one round-key
-word per lane, so they may read them only while every lane is on, whatever the compiler did this time."""
+word per lane, so they may read them only while every lane is on, whatever the compiler did this time.
+
+The out-of-line parts of the tile kernel reach its LDS through pointers that the compiler knows, so that they stay right
+wherever it places the array."""
 import re
 import subprocess
 
@@ -13,13 +16,16 @@ from paper_2608_25431_amd import build
 KERNELS = ["k_tokensILb0E", "k_tokensILb1E", "k_smallILb0E", "k_smallILb1E"]
 
 
-@pytest.fixture(scope="module")
-def assembly(tmp_path_factory):
-    out = tmp_path_factory.mktemp("asm") / "kernels.s"
-    cmd = ["/opt/rocm/bin/hipcc", f"--offload-arch={build.ARCH}", *build.HIP_FLAGS, "--cuda-device-only", "-S",
+def compiled(out, *flags):
+    cmd = ["/opt/rocm/bin/hipcc", f"--offload-arch={build.ARCH}", *build.HIP_FLAGS, "--cuda-device-only", "-S", *flags,
            "-I", f"{build.ROOT}/include", "-I", build.CSRC, build.SOURCES[0], "-o", str(out)]
     subprocess.run(cmd, check=True, capture_output=True, timeout=300)
     return out.read_text().splitlines()
+
+
+@pytest.fixture(scope="module")
+def assembly(tmp_path_factory):
+    return compiled(tmp_path_factory.mktemp("asm") / "kernels.s")
 
 
 def body(lines, kernel):
@@ -70,3 +76,10 @@ def test_lanes_are_read_while_all_are_on(assembly, kernel):
     code = body(assembly, kernel)
     assert sum(l.startswith("v_readlane_b32") for l in code) >= 12  # the loop over the rounds keeps four of them
     assert not masked_readlanes(code)
+
+
+def test_tag_mask_gets_lds_pointers(tmp_path):
+    calls = [l for l in compiled(tmp_path / "kernels.ll", "-emit-llvm") if re.search(r"call .*@_ZN4gift8tag_mask", l)]
+    assert len(calls) >= 8  # four modes, one and two teams
+    for l in calls:
+        assert len(re.findall(r"ptr addrspace\(3\) noundef", l.split("tag_mask", 1)[1])) == 2, l
