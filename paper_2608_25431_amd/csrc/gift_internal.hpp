@@ -11,7 +11,7 @@ namespace gift {
 
 // Work decomposition of the per-block kernel: one workgroup per CU (its LDS
 // tables fill most of the CU's 160 KiB), kThreads lanes each owning one
-// 16-byte block of every kThreads-block row, kRows rows per tile.
+// 16-byte block of every kThreads-block row, kRows (64 to 128) rows per tile.
 #ifndef GIFT_THREADS
 #define GIFT_THREADS 1024
 #endif

@@ -948,6 +948,7 @@ constexpr int kPrologueThreads = kExpandThreads;  // the most; 256 for tables th
 // has (with 16 in workgroups of 1024 threads 1024 segments took the same time).
 constexpr uint32_t kPrologueWaves = 4;
 constexpr uint32_t kRunTiles = 16;
+static_assert(kRows >= 64 && kRows <= 128, "a wave holds the row counts of a tile, two per lane");
 
 // Inclusive prefix sum over the wave's 64 lanes on the VALU's data-parallel
 // primitives (no LDS round trips): row shifts by 1, 2, 4 and 8 scan each row
@@ -1080,8 +1081,9 @@ __device__ bool expand_short(const SegBrief* brief, uint32_t n, const ExpandArgs
   }
   // class starts, longest first: lane k holds rows kRows - k and kRows - 64 - k
   const uint32_t ka = kRows - lane, kb = kRows - 64u - lane;
+  const bool has_b = kRows > 64 + (int)lane;
   const uint32_t na = cursor[ka] + (ka == (uint32_t)kRows ? all.x : 0u) + (ka == p ? all.y : 0u);
-  const uint32_t nb = cursor[kb] + (kb == p ? all.y : 0u);
+  const uint32_t nb = has_b ? cursor[kb] + (kb == p ? all.y : 0u) : 0u;
   const uint32_t ia = wave_incl_scan(na), ib = (uint32_t)__builtin_amdgcn_readlane((int)ia, 63) + wave_incl_scan(nb);
   const uint32_t ents = (uint32_t)__builtin_amdgcn_readlane((int)ib, 63);
   auto start = [&](uint32_t len) -> uint32_t {

@@ -16,10 +16,15 @@ from paper_2608_25431_amd import build
 KERNELS = ["k_tokensILb0E", "k_tokensILb1E", "k_smallILb0E", "k_smallILb1E"]
 
 
+def hipcc(*flags):
+    cmd = ["/opt/rocm/bin/hipcc", f"--offload-arch={build.ARCH}", *build.HIP_FLAGS, "--cuda-device-only", *flags,
+           "-I", f"{build.ROOT}/include", "-I", build.CSRC, build.SOURCES[0]]
+    return subprocess.run(cmd, capture_output=True, text=True, timeout=300)
+
+
 def compiled(out, *flags):
-    cmd = ["/opt/rocm/bin/hipcc", f"--offload-arch={build.ARCH}", *build.HIP_FLAGS, "--cuda-device-only", "-S", *flags,
-           "-I", f"{build.ROOT}/include", "-I", build.CSRC, build.SOURCES[0], "-o", str(out)]
-    subprocess.run(cmd, check=True, capture_output=True, timeout=300)
+    r = hipcc("-S", *flags, "-o", str(out))
+    assert r.returncode == 0, r.stderr
     return out.read_text().splitlines()
 
 
@@ -83,3 +88,12 @@ def test_tag_mask_gets_lds_pointers(tmp_path):
     assert len(calls) >= 8  # four modes, one and two teams
     for l in calls:
         assert len(re.findall(r"ptr addrspace\(3\) noundef", l.split("tag_mask", 1)[1])) == 2, l
+
+
+@pytest.mark.parametrize("rows,builds", [(63, False), (64, True), (129, False), (160, False)])
+def test_rows_per_tile_that_the_expansion_takes(rows, builds):
+    """The segment-table expansion keeps the row counts of a tile two per lane of a wave: tiles that it would sort into
+    the queue wrongly do not build."""
+    r = hipcc("-fsyntax-only", f"-DGIFT_ROWS={rows}")
+    assert (r.returncode == 0) == builds, r.stderr
+    assert builds or "static assertion failed" in r.stderr
