@@ -189,8 +189,12 @@ __device__ inline void aes256_encrypt_tab(uint32_t rkv, const uint32_t in[4], ui
 #undef GIFT_SB
 }
 
-// Equivalent inverse cipher with td0 and the inverse S-box passed in; lane l of
-// the wave holds word l of its round keys in dkv.  Every lane must be active.
+// One block decryption with the equivalent inverse cipher, td0 and the inverse
+// S-box passed in; lane l of the wave holds word l of its round keys in dkv, and
+// every lane must be active.  It starts with round key 14, then for rounds 13..1
+// InvSubBytes + InvShiftRows + InvMixColumns (the Td tables) + dw[round], finally
+// InvSubBytes + InvShiftRows + dw[0].  InvShiftRows takes row r of output column
+// c from input column c - r.
 __device__ inline void aes256_decrypt_tab(uint32_t dkv, const uint32_t in[4], uint32_t out[4], const uint32_t* td0,
                                           const uint8_t* isb) {
   uint32_t s0 = in[0] ^ lane_word(dkv, 56), s1 = in[1] ^ lane_word(dkv, 57), s2 = in[2] ^ lane_word(dkv, 58),
@@ -231,34 +235,6 @@ __device__ inline uint32_t inv_mix_column(uint32_t w) {
 // 14, InvMixColumns(w[i]) for rounds 1..13 (FIPS-197 Sec. 5.3.5).
 __device__ inline void aes256_dec_key_schedule(const uint32_t rk[60], uint32_t dk[60]) {
   for (int i = 0; i < 60; i++) dk[i] = (i < 4 || i >= 56) ? rk[i] : inv_mix_column(rk[i]);
-}
-
-// One AES-256 block decryption with the equivalent inverse cipher: start
-// with round key 14, then for rounds 13..1 InvSubBytes + InvShiftRows +
-// InvMixColumns (the Td tables) + dw[round], finally InvSubBytes +
-// InvShiftRows + dw[0].  InvShiftRows takes row r of output column c from
-// input column c - r.
-__device__ inline void aes256_decrypt_words(const uint32_t* __restrict__ dk, const uint32_t in[4], uint32_t out[4],
-                                            const AesConst& C) {
-  uint32_t s0 = in[0] ^ dk[56], s1 = in[1] ^ dk[57], s2 = in[2] ^ dk[58], s3 = in[3] ^ dk[59];
-#define GIFT_TD(w, k) rotl32(C.td0[((w) >> (8 * (k))) & 0xff], 8 * (k))
-  for (int r = 13; r >= 1; r--) {
-    uint32_t t0 = GIFT_TD(s0, 0) ^ GIFT_TD(s3, 1) ^ GIFT_TD(s2, 2) ^ GIFT_TD(s1, 3) ^ dk[4 * r + 0];
-    uint32_t t1 = GIFT_TD(s1, 0) ^ GIFT_TD(s0, 1) ^ GIFT_TD(s3, 2) ^ GIFT_TD(s2, 3) ^ dk[4 * r + 1];
-    uint32_t t2 = GIFT_TD(s2, 0) ^ GIFT_TD(s1, 1) ^ GIFT_TD(s0, 2) ^ GIFT_TD(s3, 3) ^ dk[4 * r + 2];
-    uint32_t t3 = GIFT_TD(s3, 0) ^ GIFT_TD(s2, 1) ^ GIFT_TD(s1, 2) ^ GIFT_TD(s0, 3) ^ dk[4 * r + 3];
-    s0 = t0;
-    s1 = t1;
-    s2 = t2;
-    s3 = t3;
-  }
-#undef GIFT_TD
-#define GIFT_ISB(w, k) ((uint32_t)C.inv_sbox[((w) >> (8 * (k))) & 0xff] << (8 * (k)))
-  out[0] = (GIFT_ISB(s0, 0) | GIFT_ISB(s3, 1) | GIFT_ISB(s2, 2) | GIFT_ISB(s1, 3)) ^ dk[0];
-  out[1] = (GIFT_ISB(s1, 0) | GIFT_ISB(s0, 1) | GIFT_ISB(s3, 2) | GIFT_ISB(s2, 3)) ^ dk[1];
-  out[2] = (GIFT_ISB(s2, 0) | GIFT_ISB(s1, 1) | GIFT_ISB(s0, 2) | GIFT_ISB(s3, 3)) ^ dk[2];
-  out[3] = (GIFT_ISB(s3, 0) | GIFT_ISB(s2, 1) | GIFT_ISB(s1, 2) | GIFT_ISB(s0, 3)) ^ dk[3];
-#undef GIFT_ISB
 }
 
 // ---------------------------------------------------------------------------

@@ -684,8 +684,8 @@ SegShape shape_of(uint64_t bytes) {
 // vector, copied to a table and from there to the ring, with the IVs byte by
 // byte, a call on 1024 segments of 4 to 16 bytes, bound by its host time, took
 // 27.6 us, now 22.7.
-void write_descs(const gift_segment* segs, uint32_t n, uint64_t row_bytes, const uint8_t* nonce_base, const void* in,
-                 const void* out, SegDesc* descs, SegBrief* brief) {
+void write_descs(const gift_segment* segs, uint32_t n, uint64_t row_bytes, const uint8_t* nonce_base, SegDesc* descs,
+                 SegBrief* brief) {
   for (uint32_t i = 0; i < n; i++) {
     const gift_segment& s = segs[i];
     SegDesc d{};
@@ -697,8 +697,7 @@ void write_descs(const gift_segment* segs, uint32_t n, uint64_t row_bytes, const
     const SegShape q = shape_of(d.len);
     d.nblocks = q.nblocks;
     if (nonce_base) make_iv(d.iv, nonce_base + 12ull * s.user, s.iv_seq);
-    const bool aligned = ((((uintptr_t)in + d.byte_off) | ((uintptr_t)out + d.byte_off)) & 15u) == 0;
-    d.flags = (aligned ? kSegAligned : 0u) | (q.small ? kSegSmall : 0u) | (q.one ? kSegOneTile : 0u);
+    d.flags = (q.small ? kSegSmall : 0u) | (q.one ? kSegOneTile : 0u);
     descs[i] = d;
     if (brief) brief[i] = SegBrief{q.nblocks, s.user};
   }
@@ -825,7 +824,7 @@ gift_status run_gcm(const gift_tensor* t, const gift_segment_table* st, gift_key
   }
 
   auto fill = [&](uint8_t* host) {
-    write_descs(st->segs, n, t->row_bytes, nonce_base, t->data, out, (SegDesc*)(host + o_desc), (SegBrief*)(host + o_br));
+    write_descs(st->segs, n, t->row_bytes, nonce_base, (SegDesc*)(host + o_desc), (SegBrief*)(host + o_br));
     ((SegBrief*)(host + o_br))[n] = SegBrief{0u, 0u};
     if (!P.zr.empty()) memcpy(host + o_zr, P.zr.data(), sizeof(ZeroRange) * P.zr.size());
     memset(host + o_qh, 0, 256);  // the queue head starts at 0
@@ -857,9 +856,7 @@ gift_status run_gcm(const gift_tensor* t, const gift_segment_table* st, gift_key
       a.pbase = nullptr;
       a.chunk_shift = 0;
       a.segs = d_desc;
-      a.n_segs = n;
       a.small_list = (const uint32_t*)(scratch + o_sl);
-      a.n_tiles = P.n_tiles;
       a.n_ents = (uint32_t)Q.cap;
       a.n_small = P.n_small;
       a.partials = (uint4*)(scratch + o_pt);
@@ -1038,7 +1035,7 @@ gift_status run_paged(const gift_paged_kv* kv, const gift_request* reqs, uint32_
     d.row_count = r.n_block_ids;
     d.user = r.user;
     d.nblocks = (uint32_t)(d.len / 16);
-    d.flags = kSegAligned | (d.nblocks <= kTileBlocks ? kSegOneTile : 0u);
+    d.flags = d.nblocks <= kTileBlocks ? kSegOneTile : 0u;
     if (d.nblocks > kTileBlocks) n_multi++;
     d.chunk0 = cpos;
     make_iv(d.iv, nonce_base + 12ull * r.user, r.iv_seq);
@@ -1113,9 +1110,7 @@ gift_status run_paged(const gift_paged_kv* kv, const gift_request* reqs, uint32_
     a.pbase = (uint8_t*)kv->base;
     a.chunk_shift = shift;
     a.segs = d_desc;
-    a.n_segs = n;
     a.small_list = (const uint32_t*)(scratch + o_sl);
-    a.n_tiles = n_tiles;
     a.n_ents = (uint32_t)Q.cap;
     a.n_small = 0;
     a.partials = (uint4*)(scratch + o_pt);
@@ -1327,7 +1322,7 @@ gift_status gift_check_owner(const gift_segment_table* st, const uint32_t* label
   SegDesc* d = (SegDesc*)lease.ptr;
   Staging* sg = staging_for(dev);
   EventMark call_ev;  // the event recorded behind the prologue
-  auto fill = [&](uint8_t* host) { write_descs(st->segs, n, 1, nullptr, nullptr, nullptr, (SegDesc*)host, nullptr); };
+  auto fill = [&](uint8_t* host) { write_descs(st->segs, n, 1, nullptr, (SegDesc*)host, nullptr); };
   e = sg ? sg->upload(d, fill, bytes, stream,
                       [&](const void* src) {
                         return launch_prologue(d, src, bytes, n, n_rows, kNoBids, labels, st->verdicts, nullptr,

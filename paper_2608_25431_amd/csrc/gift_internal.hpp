@@ -29,7 +29,7 @@ constexpr int kHPowers = kThreads + 2;                     // H^0 .. H^(kThreads
 
 // kSegOneTile: a tiled segment of at most kTileBlocks blocks; unless its tile
 // is cut into pieces, its tag needs no other entry's sum.
-enum : uint32_t { kSegAligned = 1u, kSegSmall = 2u, kSegOneTile = 4u };
+enum : uint32_t { kSegSmall = 2u, kSegOneTile = 4u };
 
 // Device descriptor of one segment (64 B), built on the host.
 struct SegDesc {
@@ -40,7 +40,7 @@ struct SegDesc {
   uint32_t iv[3];      // IV as little-endian words of its 12 bytes
   uint32_t user;
   uint32_t nblocks;    // ceil(len / 16), <= 2^32 - 2
-  uint32_t flags;      // kSegAligned | kSegSmall
+  uint32_t flags;      // kSegSmall or kSegOneTile or neither
   uint64_t chunk0;     // paged calls: index of the segment's first chunk in the chunk table
 };
 static_assert(sizeof(SegDesc) == 64, "SegDesc layout");
@@ -96,9 +96,7 @@ struct GcmArgs {
   uint8_t* pbase;
   uint32_t chunk_shift;
   const SegDesc* segs;
-  uint32_t n_segs;
   const uint32_t* small_list;  // [n_small] indices of small segments
-  uint32_t n_tiles;
   uint32_t n_ents;             // capacity of the work queue (tiles, some cut into pieces; kNoTile after the last)
   uint32_t n_small;
   uint4* partials;             // [n_tiles] GHASH partial of each tile
@@ -169,8 +167,8 @@ struct ExpandArgs {
 // and, when verdicts is not NULL, writes each segment's first verdict: the
 // owner check against labels (indexed by row, or by the block ids at byte
 // bids_off of the tables for paged calls) or OK without labels.
-// The descriptors sit at byte 0 of the tables; rows: the rows of all segments
-// that the owner check reads.  With ex, one workgroup runs
+// The descriptors sit at byte 0 of the tables; rows: the rows of the call (block
+// ids of a paged one), covered or not.  With ex, one workgroup runs
 // the segment-table expansion into *ex meanwhile, from the brief records at
 // byte brief_off of the tables.
 constexpr uint64_t kNoBids = ~0ull;

@@ -55,7 +55,7 @@ def descs_of(nblocks, rng):
     d["user"] = rng.integers(0, 1000, len(nblocks))
     small = d["nblocks"] <= SMALL_MAX_BLOCKS
     one = ~small & (d["nblocks"] <= TILE_BLOCKS)
-    d["flags"] = 1 | np.where(small, SEG_SMALL, 0) | np.where(one, SEG_ONE_TILE, 0)
+    d["flags"] = np.where(small, SEG_SMALL, 0) | np.where(one, SEG_ONE_TILE, 0)
     return d
 
 
