@@ -92,6 +92,17 @@ def test_two_teams_with_a_cut_tail(users):
     check(users, *table_of(blocks, r.integers(0, 40, n)), 16, 4)
 
 
+@pytest.mark.parametrize("long_rows", [1, 20, 40])
+def test_two_teams_reuse_their_slots(users, long_rows):
+    # about eight tiles per team, of which four can be under way at once: records and sums are used again.  Some longer
+    # tiles: whose next record is fetched after their rows (from 17 rows on), or cut into pieces (from 33)
+    r = np.random.default_rng(13)
+    n = 16 * cus()
+    blocks = r.integers(65, 1026, n)
+    blocks[r.choice(n, 40, replace=False)] = r.integers((long_rows - 1) * 1024 + 65, long_rows * 1024 + 2, 40)
+    check(users, *table_of(blocks, r.integers(0, 40, n)), 16, 14, reject=9, flips=40)
+
+
 def test_one_team_several_tiles(users):
     # tiles of 17 rows and a bit: one team, two tiles on some CUs, users change between tiles
     r = np.random.default_rng(5)
@@ -130,3 +141,20 @@ def test_paged_two_teams(users):
     labels[reqs[7][0]] += 1
     labels[reqs[n - 1][0]] += 1
     paged_case(keys, nb, kt, g, reqs, labels=labels)
+
+
+def test_paged_two_teams_reuse_their_slots(users):
+    from test_gpu_parity import paged_case, paged_geom
+    keys, nb, kt = users
+    r = np.random.default_rng(15)
+    sizes = r.integers(1, 5, 12 * cus())
+    at = np.concatenate([[0], np.cumsum(sizes)])
+    g = paged_geom("lbp", 1, 1, int(at[-1]) + 3, 2048)
+    ids = r.permutation(int(at[-1]) + 3).astype(np.uint32)
+    reqs = [(ids[at[i]:at[i + 1]], int(r.integers(0, 40)), i) for i in range(len(sizes))]
+    labels = np.full(int(at[-1]) + 3, 0xFFFFFFFF, np.uint32)
+    for b, u, _ in reqs:
+        labels[b] = u
+    for i in r.choice(len(reqs), 9, replace=False):
+        labels[reqs[int(i)][0][-1]] += 1
+    paged_case(keys, nb, kt, g, reqs, labels=labels, tamper=int(at[700]) * 2048 + 5)
