@@ -313,8 +313,8 @@ def test_random_multi_tile_tables_with_labels_and_tamper(kt3):
 def test_one_tile_segments_cut_at_the_queue_tail(kt3):
     # More one-tile segments than CUs, most longer than a 32-row piece: the
     # largest tiles (up to one per CU) are cut into pieces at the tail of the
-    # work queue, their segments lose the one-tile path and get their tags and
-    # open verdicts from the finalize pass, next to uncut ones (short
+    # work queue, and their tags and open verdicts come from the wave that
+    # completes the segment's pieces, next to uncut ones (short
     # segments, and long ones beyond the CU count).  Fused owner check with
     # two relabelled rows, then open with one ciphertext bit and one tag bit
     # flipped; the references are per-segment oracle GCM messages.
@@ -370,25 +370,16 @@ def test_one_tile_segments_cut_at_the_queue_tail(kt3):
 
 def test_one_tile_open_tamper_without_finalize(kt3):
     # At least one tile per CU, none longer than a 32-row piece: no tile is
-    # cut, every segment is an uncut one-tile segment, and the call has no
-    # finalize pass (the launch plan says so).  Open with ciphertext bits
+    # cut, every segment is an uncut one-tile segment, and no sums of several
+    # entries meet (the launch plan says so).  Open with ciphertext bits
     # flipped in three segments and tag bits in three others: the tile
     # kernel zeroes each failed tile itself (no later zeroing pass runs).
     # Whole-block rows and rows with a ragged, unaligned last block, out of
     # place and in place; every byte and verdict equals the oracle's open of
     # the tampered copy.
-    import ctypes
-    import subprocess
+    from test_launch_plan import plan_tiles_function
     keys, nb, kt = kt3
-    lib = gift.lib()
-    out = subprocess.run(["nm", "-D", "--defined-only", gift.LIB_PATH], capture_output=True, text=True).stdout
-    names = [l.split()[-1] for l in out.splitlines() if l.strip()]
-
-    class QueuePlan(ctypes.Structure):
-        _fields_ = [("cap", ctypes.c_uint64), ("grid", ctypes.c_uint32), ("finalize", ctypes.c_bool)]
-    plan = getattr(lib, next(n for n in names if n.startswith("_ZN4gift10plan_queue")))
-    plan.argtypes = [ctypes.c_uint32, ctypes.c_uint64, ctypes.c_uint32, ctypes.c_uint32, ctypes.c_uint32]
-    plan.restype = QueuePlan
+    plan = plan_tiles_function()
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     r = np.random.default_rng(31)
     for rb in (16384, 16408):
@@ -400,7 +391,8 @@ def test_one_tile_open_tamper_without_finalize(kt3):
             row += nr
         n_rows, n = row, len(table)
         tile_rows = [-(-(-(-nr * rb // 16)) // 1024) for nr in seg_rows]
-        assert not plan(n, sum(tile_rows), 0, max(tile_rows), cus).finalize
+        t = plan(n, sum(tile_rows), 0, max(tile_rows), cus, True)
+        assert (t.teams, t.workers) == (2, 1) and not t.q.finalize
         data = r.integers(0, 256, n_rows * rb, dtype=np.uint8)
         st, ct_np, tg_np, _ = oracle.seal(data, n_rows, rb, table, keys, nb)
         assert st == 0
@@ -428,7 +420,7 @@ def test_in_place_rejection_and_tamper(kt3):
     # out == data with the owner check fused: a rejected segment is zeroed in
     # place and every other byte is sealed in place, for each kind of
     # segment -- small (one wave), one-tile (tag at the tile end), one-tile
-    # cut into pieces at the queue tail (tag from the finalize pass) and
+    # cut into pieces at the queue tail (tag from the last of them) and
     # multi-tile with cut tiles; the call has more tiles than CUs, so the
     # largest tiles are cut at the tail of the work queue.  Then an in-place
     # open with one ciphertext bit and one tag bit flipped.  Every byte, tag

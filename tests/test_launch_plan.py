@@ -1,9 +1,11 @@
-"""The host's launch decisions for a call (no GPU): from per-segment counts
-only, the work queue's capacity, the tile kernel's grid, and whether the
-finalize pass may have work.  The finalize pass forms the tag of every
-segment with more than one queue entry; leaving it out when a one-tile
-segment's tile is cut would leave that segment without a tag, so it must be
-launched whenever the expansion kernel's cut can reach a one-tile segment."""
+"""The host's launch decisions for a call (no GPU), from per-segment counts
+only: teams per workgroup, the tile kernel's grid, the number of workers that
+the work queue is cut for, its capacity, and whether the sums of several
+entries of a segment meet (finalize).  Where they do, the tile partials and the
+row counts are zeroed first, and an open call ends with the zeroing pass; a
+one-tile segment whose tile were cut without that would get a wrong tag, so it
+must be so whenever the expansion kernel's cut can reach a one-tile segment.
+And how many workgroups share a record of a token call."""
 import ctypes
 import os
 import subprocess
@@ -21,6 +23,10 @@ class QueuePlan(ctypes.Structure):
     _fields_ = [("cap", ctypes.c_uint64), ("grid", ctypes.c_uint32), ("finalize", ctypes.c_bool)]
 
 
+class TilePlan(ctypes.Structure):
+    _fields_ = [("teams", ctypes.c_uint32), ("grid", ctypes.c_uint32), ("workers", ctypes.c_uint32), ("q", QueuePlan)]
+
+
 def symbol(prefix):
     """An internal function of the library, by its mangled name's prefix."""
     if not os.path.exists(gift.LIB_PATH):
@@ -30,6 +36,14 @@ def symbol(prefix):
     out = subprocess.run(["nm", "-D", "--defined-only", gift.LIB_PATH], capture_output=True, text=True).stdout
     names = [l.split()[-1] for l in out.splitlines() if l.strip()]
     return getattr(lib, next(n for n in names if n.startswith(prefix)))
+
+
+def plan_tiles_function():
+    """plan_tiles(n_tiles, rows of all tiles, segments of several tiles, most rows of a one-tile segment, CUs, open)."""
+    fn = symbol("_ZN4gift10plan_tiles")
+    fn.argtypes = [ctypes.c_uint32, ctypes.c_uint64, ctypes.c_uint32, ctypes.c_uint32, ctypes.c_uint32, ctypes.c_bool]
+    fn.restype = TilePlan
+    return fn
 
 
 @pytest.fixture(scope="module")
@@ -75,11 +89,55 @@ def test_plan_covers_the_kernel_rule(plan_queue, cus):
         assert q.finalize == need
 
 
+def a_call(r, cus):
+    """Tile count, rows, multi-tile segments and the most rows of a one-tile segment of a random table, its tile count
+    around one and two per CU and its rows around the plan's lines often."""
+    n = int(r.choice([0, 1, 2, cus // 2, cus - 1, cus, cus + 1, 2 * cus - 1, 2 * cus, 2 * cus + 1, 5 * cus]))
+    n = max(0, n + int(r.integers(-1, 2)))
+    mean = int(r.choice([1, 2, 15, 16, 17, 31, 32, 33, 64, ROWS]))
+    one = np.full(n, mean) if r.random() < 0.5 else r.integers(1, mean + 1, n)
+    if n and r.random() < 0.5:
+        p = -(-int(one.sum()) // int(r.choice([1, cus, 2 * cus])))
+        one[int(r.integers(0, n))] = np.clip(p + int(r.integers(-1, 5)), 1, ROWS)
+    tiles = r.integers(2, 5, int(r.integers(1, 3))) if r.random() < 0.3 else np.zeros(0, int)
+    rows = int(one.sum()) + int(((tiles - 1) * ROWS).sum()) + int(r.integers(1, ROWS + 1, len(tiles)).sum())
+    return n + int(tiles.sum()), rows, len(tiles), int(one.max(initial=0))
+
+
+@pytest.mark.parametrize("opened", [False, True])
+@pytest.mark.parametrize("cus", [256, 64, 7, 1])
+def test_tile_plan_covers_the_kernel_rule(cus, opened):
+    plan_tiles, r = plan_tiles_function(), np.random.default_rng(cus)
+    met = set()
+    for _ in range(3000):
+        n_tiles, rows, n_multi, one_max = a_call(r, cus)
+        t = plan_tiles(n_tiles, rows, n_multi, one_max, cus, opened)
+        if n_tiles == 0:
+            assert (t.q.cap, t.q.finalize) == (0, False)
+            continue
+        # how the kernel runs it
+        two = rows <= 16 * n_tiles if n_tiles > cus else rows <= cus
+        assert t.teams == (2 if two else 1)
+        assert t.workers in (1, cus, 2 * cus)
+        assert t.workers != 2 * cus or cus == 1 or (t.teams == 2 and n_tiles > cus)
+        assert min(cus, n_tiles) <= t.grid <= cus
+        # the queue for that many workers: its capacity, and whether the cut can give a segment several entries
+        assert t.q.cap == n_tiles + (ROWS // PIECE_ROWS - 1) * t.workers
+        assert t.q.finalize == (n_multi > 0 or can_cut_one_tile(n_tiles, rows, one_max, t.workers))
+        # one worker stands for an uncut queue, where a cut would not pay
+        if t.workers == 1 and cus > 1:
+            assert not t.q.finalize and one_max <= PIECE_ROWS
+            w = t.teams * cus if n_tiles > cus else cus
+            assert n_tiles >= w or one_max < -(-rows // w) + (3 if opened else 2)
+        met.add((t.teams, t.workers, t.q.finalize))
+    assert cus == 1 or met >= {(1, 1, False), (2, 1, False), (1, cus, True), (2, cus, True), (2, 2 * cus, True)}
+
+
 def test_examples(plan_queue):
-    # one 1.5 MiB segment on 256 CUs: cut into one-row pieces, tag from the finalize pass
+    # one 1.5 MiB segment on 256 CUs: cut into one-row pieces, tag from the last of them
     q = plan_queue(1, 96, 0, 96, 256)
     assert q.finalize and q.grid == 96
-    # 256 short one-tile segments: nothing to cut, no finalize pass
+    # 256 short one-tile segments: nothing to cut, no sums meet
     q = plan_queue(256, 256 * 4, 0, 4, 256)
     assert not q.finalize and q.grid == 256
     # more one-tile segments than CUs, longer than a quarter tile: the tail cut can reach them

@@ -10,7 +10,8 @@ padded with empty entries up to its capacity; the tiles cut are the ones the
 rule names (with fewer tiles than CUs every tile longer than ceil(rows /
 CUs); otherwise up to one per CU, the largest longer than a quarter tile);
 a one-tile segment whose tile is cut is marked cut (its tag comes from the
-finalize pass)."""
+last of its pieces).  And what the host plans a call by, from counts alone,
+agrees with what the expansion then does for that many workers."""
 import ctypes
 import subprocess
 
@@ -184,10 +185,10 @@ REGIMES = {
 
 
 @pytest.mark.parametrize("regime", sorted(REGIMES))
-@pytest.mark.parametrize("cus", [256, 64, 7, 1])
+@pytest.mark.parametrize("cus", [512, 256, 64, 7, 1])
 def test_queue_covers_every_row_once_longest_first(expand, regime, cus):
     rng = np.random.default_rng(1000 * sorted(REGIMES).index(regime) + cus)
-    for n in (1, 2, 5, 33, 200, 3000):
+    for n in (1, 2, 5, 33, 200, 400, 1000, 3000):
         d = descs_of(REGIMES[regime](rng, n), rng)
         res = plan(expand, d, cus)
         check(d, cus, *res)
@@ -215,3 +216,30 @@ def test_one_tile_segments_past_the_cu_count_share_the_tail(expand):
     d = descs_of(np.full(300, 96 * THREADS), np.random.default_rng(3))
     n_tiles, flags0, n_multi, piece, cut, ents, _, _ = plan(expand, d, 256)
     assert (piece, int(cut.sum()), len(ents), n_multi) == (PIECE_ROWS, 256, 44 + 3 * 256, 256)
+
+
+@pytest.mark.parametrize("opened", [False, True])
+def test_the_host_plan_agrees_with_the_expansion(expand, opened):
+    # Row counts around the plan's lines (16 and 32 rows, a few rows more than an even share) and tile counts around the
+    # CUs and twice the CUs: whenever the expansion gives a segment several entries the plan said so (their sums are
+    # zeroed only then, and on open the zeroing pass runs only then), and the queue holds every entry.
+    from test_launch_plan import plan_tiles_function
+    plan_tiles, cus = plan_tiles_function(), 256
+    rng = np.random.default_rng(4)
+    agree = [0, 0]
+    for n in (1, 3, 200, 255, 256, 257, 300, 511, 512, 513, 700, 1500):
+        for top in (1, 2, 3, 4, 15, 16, 17, 31, 32, 33, 40, ROWS, 3 * ROWS):
+            rows = rng.integers(1, top + 1, n) if rng.random() < 0.5 else np.full(n, top)
+            if rng.random() < 0.3:
+                rows[rng.integers(0, n)] += int(rng.integers(1, 40))
+            d = descs_of(rows * THREADS - rng.integers(0, THREADS - SMALL_MAX_BLOCKS, n), rng)
+            tiled = [int(m) for m in d["nblocks"] if m > SMALL_MAX_BLOCKS]
+            tiles = [-(-m // TILE_BLOCKS) for m in tiled]
+            n_rows = [(t - 1) * ROWS + tile_rows(m, t - 1) for m, t in zip(tiled, tiles)]
+            one = [x for x, t in zip(n_rows, tiles) if t == 1]
+            t = plan_tiles(sum(tiles), sum(n_rows), sum(1 for x in tiles if x > 1), max(one, default=0), cus, opened)
+            n_tiles, _, n_multi, _, cut, ents, _, _ = plan(expand, d, t.workers)
+            assert t.q.finalize == (n_multi > 0), (n, top)
+            assert len(ents) <= t.q.cap and t.grid <= cus and t.grid * t.teams >= min(len(ents), t.workers)
+            agree[int(t.q.finalize)] += 1
+    assert min(agree) > 20
