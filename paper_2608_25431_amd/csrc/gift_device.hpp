@@ -1,6 +1,6 @@
 // Device-side building blocks for segmented AES-256-GCM on gfx950:
-// compile-time AES tables, the AES-256 key schedule, a table-free AES block
-// function for setup/finalize work, GF(2^128) arithmetic in GCM bit order,
+// compile-time AES tables, the AES-256 key schedule, AES block functions for
+// key setup, small segments and tokens, GF(2^128) arithmetic in GCM bit order,
 // and small wave-level helpers.  The per-block hot loop lives in
 // gift_kernels.hip and uses LDS-resident tables instead.
 #pragma once
@@ -115,9 +115,8 @@ __device__ inline void aes256_key_schedule(const uint8_t* __restrict__ key, uint
   }
 }
 
-// One AES-256 block from tables in global/constant memory.  Used only where
-// a few blocks per segment are needed (E_K(J0), H, small segments).
-// State words are columns (little-endian), as above.
+// One AES-256 block from tables in constant memory, for key setup (H).  State
+// words are columns (little-endian), as above.
 __device__ inline void aes256_encrypt_words(const uint32_t* __restrict__ rk, const uint32_t in[4], uint32_t out[4],
                                             const AesConst& C) {
   uint32_t s0 = in[0] ^ rk[0], s1 = in[1] ^ rk[1], s2 = in[2] ^ rk[2], s3 = in[3] ^ rk[3];

@@ -41,8 +41,9 @@ size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // What the host decides for a call's launches, from per-segment counts only
 // (the tile tables and the work queue are built on the device by
-// launch_expand): the queue's capacity, the tile kernel's grid and whether
-// some segment may have more than one entry (finalize: its entries' sums meet).
+// launch_expand), given the workers that the queue is cut for: its capacity,
+// the tile kernel's grid and whether some segment may have more than one entry
+// (finalize: its entries' sums meet).
 struct QueuePlan {
   uint64_t cap = 0;
   uint32_t grid = 0;
@@ -81,9 +82,14 @@ TilePlan plan_tiles(uint32_t n_tiles, uint64_t tile_rows_all, uint32_t n_multi, 
   // multiplies per tile, and one tile's end under the other's rows.  Seal calls
   // with one team / with two, in us: 1024 segments of 1 row 67.9 / 53.5, of 4
   // rows 110 / 98, of 16 rows 307 / 296; 300 of 16 rows 152 / 123.  In longer
-  // tiles the end does not show (64 rows: 1137 / 1134), and at the queue's end
-  // a team alone on its CU does not fill the LDS (600 segments of 20 rows: 270
-  // / 283).  With no more tiles than CUs the second team would have none;
+  // tiles the end hardly shows (1024 of 20 rows 386 / 378, of 64 1137 / 1134),
+  // and at the queue's end a team alone on its CU does not fill the LDS: from
+  // 17 rows on two are slower where the tiles don't divide evenly (600 segments
+  // of 20 rows 269 / 280, 700 278 / 286).  The line does not look at how they
+  // divide: between one and two tiles per CU, where two teams' queue is cut for
+  // twice the CUs, they would be faster past it, too (300 segments of 20 rows
+  // 183 / 144, of 32 276 / 213, 400 of 24 217 / 207, 511 of 20 202 / 195).
+  // With no more tiles than CUs the second team would have none;
   // then one team, except in calls of so few rows that each CU gets one at
   // most: 8 waves multiply sooner than 16 (11 rows: 29.4 / 27.9).
   if (n_tiles > cus ? tile_rows_all <= (uint64_t)kTwoTeamRows * n_tiles : tile_rows_all <= cus) t.teams = 2;
