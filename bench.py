@@ -6,7 +6,7 @@ users, sequence lengths uniform in [128, 2048], one segment per request of
 32 rows (layers) x 64 KiB per 16-token block, ~9.1 GB of bf16 -- sealed with
 the owner-label check fused.  One step is one gift_seal call over the whole
 tensor: validation, staging, owner check, segment-table expansion, the
-per-block AES-CTR/GHASH kernel and the per-segment tag finalize.  Inputs are
+per-block AES-CTR/GHASH kernel, which forms the per-segment tags.  Inputs are
 resident in HBM before timing starts.  The timed pass runs the steps back to
 back with no event between them; a second pass of the same steps with
 events on the launch stream gives the median step and the per-block
