@@ -541,6 +541,11 @@ __global__ __launch_bounds__(kThreads) void k_gcm_tiles(GcmArgs a) {
   //     round keys: three dependent loads, up to 12k clocks).  In a tile of
   //     more than kLateRows rows it does so after its rows, so that a
   //     workgroup claims no more than it is about to run; else before them.
+  //     Early in every tile of up to 16 rows, a workgroup that came from a
+  //     longer one claimed two short entries at once, and others went without:
+  //     seals of 256 segments of 48 rows (32-row pieces, then 16) 286 us per
+  //     call, late from 3 rows on 223; 531 segments of 1-60 rows 352 / 304, 795
+  //     of them 511 / 463; in tiles of 1-4 rows no difference.
   //     The slot held tile k - 3, which is finished.
   //   - a wave that has done its rows of tile k multiplies, adds to the tile's
   //     sum and goes on to tile k + 1, whose first row needs no GHASH table.
@@ -553,7 +558,7 @@ __global__ __launch_bounds__(kThreads) void k_gcm_tiles(GcmArgs a) {
   // two teams (81 with one); 2 requests, 45 tiles cut into 25-row pieces, 159.9
   // -> 144.2 us; 128-row tiles +0.7%.
   constexpr uint32_t kRecWave = 0, kTabWave = kTeamWaves - 1;
-  constexpr int kLateRows = 16 * TEAMS;
+  constexpr int kLateRows = 2 * TEAMS;  // 2 rows of 1024 blocks
   constexpr bool kPair = TEAMS == 2;  // the second entry is 2W - 1 - w
   const uint32_t W = TEAMS * gridDim.x, w = blockIdx.x + team * gridDim.x;
   const TileEnt e0 = w < a.n_ents ? a.tile_order[w] : TileEnt{kNoTile, 0u, 0u, 0u};

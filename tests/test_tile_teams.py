@@ -95,7 +95,7 @@ def test_two_teams_with_a_cut_tail(users):
 @pytest.mark.parametrize("long_rows", [1, 20, 40])
 def test_two_teams_reuse_their_slots(users, long_rows):
     # about eight tiles per team, of which four can be under way at once: records and sums are used again.  Some longer
-    # tiles: whose next record is fetched after their rows (from 17 rows on), or cut into pieces (from 33)
+    # tiles: whose next record is fetched after their rows (from 3 rows on), or cut into pieces (from 33)
     r = np.random.default_rng(13)
     n = 16 * cus()
     blocks = r.integers(65, 1026, n)
