@@ -69,6 +69,7 @@ QueuePlan plan_queue(uint32_t n_tiles, uint64_t tile_rows_all, uint32_t n_multi,
 // How the tile kernel runs a call: teams per workgroup, workgroups, and the
 // number of workers the queue is cut for (the expansion's "CUs").
 constexpr uint32_t kTwoTeamRows = 16;  // two teams for tiles of up to this many rows on average
+constexpr uint32_t kTwoTeamRowsAt3 = 7;  // with two to three tiles per CU
 
 struct TilePlan {
   uint32_t teams = 1, grid = 0, workers = 0;
@@ -85,14 +86,19 @@ TilePlan plan_tiles(uint32_t n_tiles, uint64_t tile_rows_all, uint32_t n_multi, 
   // tiles the end hardly shows (1024 of 20 rows 386 / 378, of 64 1137 / 1134),
   // and at the queue's end a team alone on its CU does not fill the LDS: from
   // 17 rows on two are slower where the tiles don't divide evenly (600 segments
-  // of 20 rows 269 / 280, 700 278 / 286).  The line does not look at how they
+  // of 20 rows 269 / 280, 700 278 / 286).  The line there does not look at how they
   // divide: between one and two tiles per CU, where two teams' queue is cut for
   // twice the CUs, they would be faster past it, too (300 segments of 20 rows
   // 183 / 144, of 32 276 / 213, 400 of 24 217 / 207, 511 of 20 202 / 195).
+  // With two to three tiles per CU one team needs three rounds, and of two teams'
+  // second round most CUs have one tile, so that two pay in shorter tiles only:
+  // 640 segments of 4 rows 81 / 78, of 7 116 / 117, of 10 152 / 155; 513 of 16
+  // rows 216 / 227, 768 227 / 240.
   // With no more tiles than CUs the second team would have none;
   // then one team, except in calls of so few rows that each CU gets one at
   // most: 8 waves multiply sooner than 16 (11 rows: 29.4 / 27.9).
-  if (n_tiles > cus ? tile_rows_all <= (uint64_t)kTwoTeamRows * n_tiles : tile_rows_all <= cus) t.teams = 2;
+  const uint64_t two_rows = n_tiles > 2 * cus && n_tiles <= 3 * cus ? kTwoTeamRowsAt3 : kTwoTeamRows;
+  if (n_tiles > cus ? tile_rows_all <= two_rows * n_tiles : tile_rows_all <= cus) t.teams = 2;
   t.workers = n_tiles > cus ? t.teams * cus : cus;
   // While no tile of a call of one-tile segments is cut, no sums need to meet.
   // A row takes a team about 5 us, the meeting of a segment's pieces about as

@@ -92,9 +92,9 @@ def test_plan_covers_the_kernel_rule(plan_queue, cus):
 def a_call(r, cus):
     """Tile count, rows, multi-tile segments and the most rows of a one-tile segment of a random table, its tile count
     around one and two per CU and its rows around the plan's lines often."""
-    n = int(r.choice([0, 1, 2, cus // 2, cus - 1, cus, cus + 1, 2 * cus - 1, 2 * cus, 2 * cus + 1, 5 * cus]))
+    n = int(r.choice([0, 1, 2, cus // 2, cus - 1, cus, cus + 1, 2 * cus - 1, 2 * cus, 2 * cus + 1, 3 * cus, 5 * cus]))
     n = max(0, n + int(r.integers(-1, 2)))
-    mean = int(r.choice([1, 2, 15, 16, 17, 31, 32, 33, 64, ROWS]))
+    mean = int(r.choice([1, 2, 7, 8, 15, 16, 17, 31, 32, 33, 64, ROWS]))
     one = np.full(n, mean) if r.random() < 0.5 else r.integers(1, mean + 1, n)
     if n and r.random() < 0.5:
         p = -(-int(one.sum()) // int(r.choice([1, cus, 2 * cus])))
@@ -116,7 +116,7 @@ def test_tile_plan_covers_the_kernel_rule(cus, opened):
             assert (t.q.cap, t.q.finalize) == (0, False)
             continue
         # how the kernel runs it
-        two = rows <= 16 * n_tiles if n_tiles > cus else rows <= cus
+        two = rows <= (7 if 2 * cus < n_tiles <= 3 * cus else 16) * n_tiles if n_tiles > cus else rows <= cus
         assert t.teams == (2 if two else 1)
         assert t.workers in (1, cus, 2 * cus)
         assert t.workers != 2 * cus or cus == 1 or (t.teams == 2 and n_tiles > cus)
