@@ -110,6 +110,10 @@ TilePlan plan_tiles(uint32_t n_tiles, uint64_t tile_rows_all, uint32_t n_multi, 
   if (n_multi == 0 && one_rows_max <= (uint32_t)kPieceRows &&
       (n_tiles >= t.workers || one_rows_max < p + (open ? 3u : 2u)))
     t.workers = 1;
+  else if (n_tiles == t.workers)
+    // A tile for every worker: cut evenly, as for fewer tiles, not into 32-row
+    // pieces and what is left (256 segments of 34 rows 157 / 182 us per call).
+    t.workers++;
   t.q = plan_queue(n_tiles, tile_rows_all, n_multi, one_rows_max, t.workers);
   t.grid = std::min(cus, std::max(t.q.grid, n_tiles));
   return t;
@@ -816,10 +820,11 @@ gift_status run_gcm(const gift_tensor* t, const gift_segment_table* st, gift_key
     // Which calls fit is part of the interface, so it does not depend on how
     // the tile kernel runs them: it goes by a queue for one worker per CU and
     // 16 B per segment beside the tables.  The queue of a two-team call has
-    // 3 * CUs entries more, and those 16 B pay for them: two teams run more
-    // tiles than CUs of up to 16 rows on average, so at least 7 segments per 8
-    // tiles, and a table of too few segments to pay (768 for 256 CUs) is far
-    // from the limit, with at most half of it staged and 40 KB beside that.
+    // 3 * CUs entries more (or 3 more than that, or than with one team), and
+    // those 16 B pay for them: two teams run more tiles than CUs of up to 16 rows
+    // on average, so at least 7 segments per 8 tiles, and a table of too few
+    // segments to pay (771 for 256 CUs) is far from the limit, with at most half
+    // of it staged and 40 KB beside that.
     const uint64_t cap1 = P.n_tiles ? queue_capacity(P.n_tiles, cus) : 1;
     const size_t need = std::max(bytes, bytes - (o_pt - o_to) + align256(sizeof(TileEnt) * cap1) + align256(16ull * (n ? n : 1)));
     if (need > kStaticScratchBytes || o_st > Staging::kMaxStaged)

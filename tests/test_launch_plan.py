@@ -118,8 +118,8 @@ def test_tile_plan_covers_the_kernel_rule(cus, opened):
         # how the kernel runs it
         two = rows <= (7 if 2 * cus < n_tiles <= 3 * cus else 16) * n_tiles if n_tiles > cus else rows <= cus
         assert t.teams == (2 if two else 1)
-        assert t.workers in (1, cus, 2 * cus)
-        assert t.workers != 2 * cus or cus == 1 or (t.teams == 2 and n_tiles > cus)
+        w = t.teams * cus if n_tiles > cus else cus
+        assert t.workers in (1, w + (n_tiles == w))  # cut evenly also with a tile for each
         assert min(cus, n_tiles) <= t.grid <= cus
         # the queue for that many workers: its capacity, and whether the cut can give a segment several entries
         assert t.q.cap == n_tiles + (ROWS // PIECE_ROWS - 1) * t.workers
@@ -127,7 +127,6 @@ def test_tile_plan_covers_the_kernel_rule(cus, opened):
         # one worker stands for an uncut queue, where a cut would not pay
         if t.workers == 1 and cus > 1:
             assert not t.q.finalize and one_max <= PIECE_ROWS
-            w = t.teams * cus if n_tiles > cus else cus
             assert n_tiles >= w or one_max < -(-rows // w) + (3 if opened else 2)
         met.add((t.teams, t.workers, t.q.finalize))
     assert cus == 1 or met >= {(1, 1, False), (2, 1, False), (1, cus, True), (2, cus, True), (2, 2 * cus, True)}

@@ -240,6 +240,6 @@ def test_the_host_plan_agrees_with_the_expansion(expand, opened):
             t = plan_tiles(sum(tiles), sum(n_rows), sum(1 for x in tiles if x > 1), max(one, default=0), cus, opened)
             n_tiles, _, n_multi, _, cut, ents, _, _ = plan(expand, d, t.workers)
             assert t.q.finalize == (n_multi > 0), (n, top)
-            assert len(ents) <= t.q.cap and t.grid <= cus and t.grid * t.teams >= min(len(ents), t.workers)
+            assert len(ents) <= t.q.cap and t.grid <= cus and t.grid * t.teams >= min(len(ents), t.teams * cus)
             agree[int(t.q.finalize)] += 1
     assert min(agree) > 20
